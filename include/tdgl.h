@@ -176,7 +176,7 @@ tdgl_status tdgl_set_gradient(tdgl_ctx *ctx, double G11, double G12, double G44,
 
 /* Build the electrostatic interaction tensor on the device in FP64 (eq 6 for
  * cell-wise uniform P: cell-averaged dipolar tensor, closed form for touching
- * cells and Gauss-Legendre quadrature elsewhere; periodic dimensions sum
+ * cells and Gauss quadrature elsewhere; periodic dimensions sum
  * lattice images |offset| <= (mimg + 1/2) * n and fix the in-plane k = 0
  * mode to its infinite-lattice value), transform it and keep one octant of
  * the real spectrum with -kappa/(mx my mz) folded in.  Needs set_scales.

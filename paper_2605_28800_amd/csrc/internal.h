@@ -17,7 +17,12 @@ __host__ __device__ constexpr int tw_off(int L)
 {
     return (L & (L - 1)) == 0 ? L : 2 * MAXLEN + L;
 }
-constexpr int GL_MAXN = 24;    // Gauss-Legendre table rows/columns
+// quadrature tables of the tensor build: row n (< GL_MAXN) of nodes and of
+// weights for the n-point Gauss rule of the tent weight, and for the two
+// n-point Gauss-Legendre rules of its halves (2 n nodes)
+constexpr int GL_MAXN = 24;
+constexpr int GL_HALF = 2 * GL_MAXN * GL_MAXN;                   // start of the second kind
+constexpr int GL_ENTRIES = GL_HALF + 2 * GL_MAXN * 2 * GL_MAXN;
 
 enum { PREC_F32 = 0, PREC_F64 = 1 };
 
@@ -170,9 +175,10 @@ hipError_t launch_convert(int src_prec, const void *src, int dst_prec, void *dst
 hipError_t launch_zero_layers(int prec, void *P, const void *coef, const Geom &g, hipStream_t s);
 
 // tensor construction (FP64)
-hipError_t launch_tensor_real(const Geom &g, unsigned pmask, int mimg, double dx, double dy,
-                              double dz, const double *gl_t, const double *gl_w, double *R,
-                              hipStream_t s);
+// octant: temporary of tensor_octant_bytes
+size_t tensor_octant_bytes(const Geom &g);
+hipError_t launch_tensor_real(const Geom &g, int mimg, double dx, double dy, double dz,
+                              const double *gl, double *octant, double *R, hipStream_t s);
 hipError_t launch_tensor_k0(const Geom &g, unsigned pmask, double *R, double *sums,
                             hipStream_t s);
 hipError_t launch_tensor_octant(int prec, const Geom &g, const void *C, double scale, void *Nt,

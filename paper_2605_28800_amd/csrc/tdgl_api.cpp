@@ -178,7 +178,7 @@ Layout layout_of(const tdgl_ctx *c, int scheme)
     L.kp = take(sizeof(KParams<double>));
     L.twf = take((size_t)TW_ENTRIES * 2 * sizeof(float));
     L.twd = take((size_t)TW_ENTRIES * 2 * sizeof(double));
-    L.gl = take((size_t)2 * GL_MAXN * GL_MAXN * sizeof(double));
+    L.gl = take((size_t)GL_ENTRIES * sizeof(double));
     L.partials = take((size_t)c->nblocks * g.nb * 8 * sizeof(double));
     L.flag = take(sizeof(int));
     L.res = take((size_t)8 * g.nb * sizeof(double));
@@ -194,40 +194,90 @@ Layout layout_of(const tdgl_ctx *c, int scheme)
 
 Layout layout_of(const tdgl_ctx *c) { return layout_of(c, c->scheme); }
 
-// Gauss-Legendre nodes and weights on [0,1] (Newton on the Legendre
-// recurrence in long double); row n of the tables holds n nodes.
-void gauss_legendre_tables(double *t, double *w)
+// Legendre nodes on [0, 1] (Newton on the recurrence) and weights
+void gauss_legendre(int n, long double *x, long double *w)
 {
-    for (int i = 0; i < GL_MAXN * GL_MAXN; ++i) t[i] = w[i] = 0.0;
+    for (int i = 0; i < n; ++i) {
+        long double u = cosl(3.14159265358979323846264338327950288L * (i + 0.75L) / (n + 0.5L));
+        long double dp = 1.0L;
+        for (int it = 0; it < 50; ++it) {
+            long double p0 = 1.0L, p1 = u;
+            for (int k = 2; k <= n; ++k) {
+                const long double p2 = ((2 * k - 1) * u * p1 - (k - 1) * p0) / k;
+                p0 = p1;
+                p1 = p2;
+            }
+            dp = n * (u * p1 - p0) / (u * u - 1.0L);
+            u -= p1 / dp;
+        }
+        x[i] = 0.5L * (u + 1.0L);
+        w[i] = 1.0L / ((1.0L - u * u) * dp * dp);
+    }
+}
+
+// Quadrature against the tent weight 1 - |u| on [-1, 1] (layout in
+// internal.h).  Its Gauss rules: the monic orthogonal polynomials p_{k+1} =
+// u p_k - b_k p_{k-1} of the even weight come from their defining inner
+// products (Stieltjes' procedure; an inner product of polynomials of total
+// degree below 2 GL_MAXN is exact with GL_MAXN + 1 Legendre nodes on each half),
+// the roots by bisection between those of the previous polynomial, the
+// weights as 1 / sum of the squared orthonormal polynomials; in long double.
+void quadrature_tables(double *tab)
+{
+    typedef long double ld;
+    constexpr int Q = GL_MAXN + 1;
+    ld gx[Q], gw[Q];
+    std::fill(tab, tab + GL_ENTRIES, 0.0);
+    for (int n = 1; n < GL_MAXN; ++n) {           // Legendre rules of the two halves
+        double *t = tab + GL_HALF + n * 2 * GL_MAXN, *w = t + GL_MAXN * 2 * GL_MAXN;
+        gauss_legendre(n, gx, gw);
+        for (int i = 0; i < n; ++i) {
+            t[i] = (double)gx[i];
+            t[n + i] = -(double)gx[i];
+            w[i] = w[n + i] = (double)(gw[i] * (1 - gx[i]));
+        }
+    }
+    gauss_legendre(Q, gx, gw);
+    ld b[GL_MAXN] = {0}, norm[GL_MAXN];           // b_k and |p_k|^2
+    auto eval = [&](int n, ld x) {                // p_n(x)
+        ld p0 = 0, p1 = 1;
+        for (int k = 0; k < n; ++k) {
+            const ld p2 = x * p1 - (k ? b[k] * p0 : 0);
+            p0 = p1;
+            p1 = p2;
+        }
+        return p1;
+    };
+    for (int k = 0; k < GL_MAXN; ++k) {
+        norm[k] = 0;
+        for (int i = 0; i < Q; ++i) {             // p_k^2 is even
+            const ld v = eval(k, gx[i]);
+            norm[k] += 2 * gw[i] * (1 - gx[i]) * v * v;
+        }
+        if (k) b[k] = norm[k] / norm[k - 1];      // used by p_{k+1} on
+    }
+    double *t = tab, *w = tab + GL_MAXN * GL_MAXN;
+    ld root[GL_MAXN + 1], prev[GL_MAXN + 1];
     for (int n = 1; n < GL_MAXN; ++n) {
         for (int i = 0; i < n; ++i) {
-            long double x = cosl(3.14159265358979323846264338327950288L * (i + 0.75L) / (n + 0.5L));
-            long double dp = 1.0L;
-            for (int it = 0; it < 100; ++it) {
-                long double p0 = 1.0L, p1 = x;
-                for (int k = 2; k <= n; ++k) {
-                    long double p2 = ((2.0L * k - 1.0L) * x * p1 - (k - 1.0L) * p0) / k;
-                    p0 = p1;
-                    p1 = p2;
-                }
-                if (n == 1) { p0 = 1.0L; p1 = x; }
-                dp = n * (x * p1 - p0) / (x * x - 1.0L);
-                long double dx = p1 / dp;
-                x -= dx;
-                if (fabsl(dx) < 1e-19L) break;
+            ld lo = i == 0 ? -1 : prev[i - 1], hi = i == n - 1 ? 1 : prev[i];
+            const bool up = eval(n, lo) < 0;
+            for (int it = 0; it < 70; ++it) {
+                const ld mid = 0.5L * (lo + hi);
+                if ((eval(n, mid) < 0) == up) lo = mid;
+                else hi = mid;
             }
-            {   // final derivative at the converged root
-                long double p0 = 1.0L, p1 = x;
-                for (int k = 2; k <= n; ++k) {
-                    long double p2 = ((2.0L * k - 1.0L) * x * p1 - (k - 1.0L) * p0) / k;
-                    p0 = p1;
-                    p1 = p2;
-                }
-                dp = n * (x * p1 - p0) / (x * x - 1.0L);
+            root[i] = 0.5L * (lo + hi);
+        }
+        for (int i = 0; i < n; ++i) {
+            prev[i] = root[i];
+            ld s = 0;
+            for (int k = 0; k < n; ++k) {
+                const ld v = eval(k, root[i]);
+                s += v * v / norm[k];
             }
-            const long double wt = 2.0L / ((1.0L - x * x) * dp * dp);
-            t[n * GL_MAXN + i] = (double)(0.5L * (x + 1.0L));
-            w[n * GL_MAXN + i] = (double)(0.5L * wt);
+            t[n * GL_MAXN + i] = (double)root[i];
+            w[n * GL_MAXN + i] = (double)(1 / s);
         }
     }
 }
@@ -289,8 +339,8 @@ tdgl_status ensure_device(tdgl_ctx *c)
     if (c->scheme == TDGL_RK45) c->rkbuf = b + L.extra;
     auto twf = twiddle_table<float>();
     auto twd = twiddle_table<double>();
-    std::vector<double> gl(2 * GL_MAXN * GL_MAXN);
-    gauss_legendre_tables(gl.data(), gl.data() + GL_MAXN * GL_MAXN);
+    std::vector<double> gl(GL_ENTRIES);
+    quadrature_tables(gl.data());
     HIP_TRY(c, hipMemcpy(c->twf, twf.data(), twf.size() * sizeof(float), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemcpy(c->twd, twd.data(), twd.size() * sizeof(double), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemcpy(c->gl, gl.data(), gl.size() * sizeof(double), hipMemcpyHostToDevice));
@@ -959,15 +1009,16 @@ tdgl_status tdgl_build_tensor(tdgl_ctx *c, int mimg)
     void *C = nullptr;
     if (hipMalloc(&R, 6 * nreal * sizeof(double)) != hipSuccess)
         return fail(c, TDGL_E_NOMEM, "tensor build: hipMalloc failed");
-    if (hipMalloc(&C, 6 * ncplx * 2 * sizeof(double)) != hipSuccess) {
+    if (hipMalloc(&C, std::max(6 * ncplx * 2 * sizeof(double), tensor_octant_bytes(g))) !=
+        hipSuccess) {
         (void)hipFree(R);
         return fail(c, TDGL_E_NOMEM, "tensor build: hipMalloc failed");
     }
     const double l0 = std::sqrt(c->G110 / c->alpha_ref);
     const double kappa = 1.0 / (EPS0 * c->eps_b * c->alpha_ref);
-    hipError_t e = launch_tensor_real(g, c->pmask, mimg, c->d[0] / l0, c->d[1] / l0,
-                                      c->d[2] / l0, c->gl, c->gl + GL_MAXN * GL_MAXN, R,
-                                      c->stream);
+    // the octant is read out into R before the spectrum is written over it
+    hipError_t e = launch_tensor_real(g, mimg, c->d[0] / l0, c->d[1] / l0, c->d[2] / l0, c->gl,
+                                      static_cast<double *>(C), R, c->stream);
     if (e == hipSuccess) e = launch_tensor_k0(g, c->pmask, R, nullptr, c->stream);
     // spectrum C[kx][q][mz][my]: x pass (kx-major), y rows, z columns
     const long long rows = 6LL * g.mz * g.my;
