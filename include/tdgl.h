@@ -240,8 +240,8 @@ tdgl_status tdgl_set_graph_chunk(tdgl_ctx *ctx, int steps);
 
 /* FFT pass layout: path 0 (default) fuses the y pass, the z pass with the
  * tensor multiply and the inverse y pass into one kernel per kx plane when
- * that plane fits in one work-group's LDS, and uses three kernels
- * otherwise; path 1 always uses the three kernels.  Results agree to
+ * that plane is small (at most 512 points per component), and uses three
+ * kernels otherwise; path 1 always uses the three kernels.  Results agree to
  * rounding.  tdgl_get_fft_path reports whether the fused kernel is in use
  * (known after the first call that touches the device). */
 tdgl_status tdgl_set_fft_path(tdgl_ctx *ctx, int path);

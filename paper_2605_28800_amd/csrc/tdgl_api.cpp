@@ -364,11 +364,20 @@ tdgl_status ensure_device(tdgl_ctx *c)
 
 const void *tw(const tdgl_ctx *c) { return c->prec == PREC_F32 ? c->twf : c->twd; }
 
-// The fused plane pass is used when one kx plane of the three components
-// (plus the z-pass scratch) fits in the LDS of one work-group.
+// The fused plane pass is used for planes of at most PLANE_POINTS (z, ky)
+// points per component that fit in the LDS of one work-group.  One group holds
+// a whole plane, so larger ones leave few waves per CU; smaller ones are
+// cheaper than two more launches.  Heun steps, fused against three passes:
+// 8x8x8 (128 points) 25.1 / 28.4 us, 32x32x8 film (256) 27.2 / 30.4, 32x32x8
+// box FP64 (512) 33.4 / 33.6; 100x30x12 box (768) 47.5 / 42.0, 64x64x16 film
+// (1024) 41.0 / 36.0, 75x50x21 box (2688) 126 / 83, 24 boxes of 32x32x32 (2048)
+// 212 / 148.  The rule does not look at the batch, so that an instance
+// rounds as it does alone.
+constexpr int PLANE_POINTS = 512;
+
 void choose_path(tdgl_ctx *c)
 {
-    c->use_plane = c->fft_path == 0 &&
+    c->use_plane = c->fft_path == 0 && c->g.nz * c->g.my <= PLANE_POINTS &&
                    launch_plane(c->prec, c->g, nullptr, nullptr, nullptr, c->lds_max, nullptr,
                                 true) == hipSuccess;
 }
