@@ -17,13 +17,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ inline float bf2f(bf16_t h) { return __uint_as_float((uint32_t)h << 16); }
-// round to nearest, ties to even (finite inputs)
+// round to nearest, ties to even (one conversion instruction)
 __device__ inline bf16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
+  union { __bf16 h; bf16_t u; } v;
+  v.h = (__bf16)f;
+  return v.u;
 }
-__device__ inline float act(float z) { return z > 0.f ? z : SLOPE * z; }
+__device__ inline float act(float z) { return fmaxf(z, SLOPE * z); }
 __device__ inline float act_slope(bf16_t y) { return bf2f(y) > 0.f ? 1.f : SLOPE; }
 
 __device__ inline bf16x8 load8(const bf16_t *p) { return *reinterpret_cast<const bf16x8 *>(p); }
@@ -61,20 +61,31 @@ __device__ inline long long gather_index(const Pos &p, int dz, int dy, int dx, i
 }
 
 // ----------------------------------------------------------------- conv
-// One work-group: 4 waves x 16 * NB output positions, 16 * MB output
-// channels (blockIdx.y selects the channel block).  K = 27 * cin_p runs in
-// steps of 32: each lane gathers 8 consecutive input channels of one tap
+// element index of the 8 packed weights of rows 16 m + col, tap t, channels
+// ci .. ci + 7 (ci a multiple of 8); co16: 16-row blocks
+__device__ __forceinline__ size_t packed_at(int co16, int m, int col, int t, int ci) {
+  const int c = ci >> 4, kq = 2 * (t & 1) + ((ci >> 3) & 1);
+  return (((size_t)c * 14 + (t >> 1)) * co16 + m) * 512 + (kq * 16 + col) * 8;
+}
+
+// Small grids.  One work-group: 4 waves x 16 * NB output positions, 16 * MB
+// output channels (blockIdx.y selects the channel block).  K = 27 * cin_p runs
+// in steps of 32: each lane gathers 8 consecutive input channels of one tap
 // for each of its NB position columns, and 8 consecutive weights per 16-row
 // block; the operands of step k + 1 are loaded while step k's MFMAs run.
 template <int MB, int NB>
-__device__ __forceinline__ void conv_operands(const ConvArgs &a, const bf16_t *wrow, int kp,
+__device__ __forceinline__ void conv_operands(const ConvArgs &a, int co_blk, int col, int kp,
                                               int lc, int k0, int kq, const Pos *p,
                                               const bool *inb, bf16x8 *av, bf16x8 *bv) {
   const int k = k0 + 8 * kq;
   const bool kv = k < kp;
   const int t = k >> lc, ci = k & (a.cin_p - 1);
   const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-  for (int mb = 0; mb < MB; ++mb) av[mb] = kv ? load8(wrow + (size_t)mb * 16 * kp + k) : zero8();
+  for (int mb = 0; mb < MB; ++mb) {
+    const size_t o = a.packed ? packed_at(a.cout_p >> 4, (co_blk >> 4) + mb, col, t, ci)
+                              : (size_t)(co_blk + mb * 16 + col) * kp + k;
+    av[mb] = kv ? load8(a.w + o) : zero8();
+  }
   for (int j = 0; j < NB; ++j) {
     long long src = -1;
     if (kv && inb[j]) src = gather_index(p[j], dz, dy, dx, a.lx, a.ly, a.lz, a.in_up2);
@@ -82,44 +93,61 @@ __device__ __forceinline__ void conv_operands(const ConvArgs &a, const bf16_t *w
   }
 }
 
-// epilogue of one lane: channels co0 .. co0 + 3 of output position n (p its
-// coordinates; ls = log2 of the cells per sample)
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  union { bf16x2 h; uint32_t u; } v;
+  v.h = __builtin_convertvector((floatx2){lo, hi}, bf16x2);
+  return v.u;
+}
+
+// Epilogue of one lane: channels co0 .. co0 + 3 of an output position, in three
+// parts, so that a kernel loads the bias and the addends of all its positions
+// before the first store (a load behind a store waits for it).  o: element
+// offset of channel co0 at the position.
+template <int EPI>
+__device__ __forceinline__ floatx4 conv_bias(const ConvArgs &a, int co0) {
+  if (EPI == EPI_ACT || EPI == EPI_ACT_SKIP || EPI == EPI_P)
+    return *reinterpret_cast<const floatx4 *>(a.bias + co0);
+  return floatx4{0.f, 0.f, 0.f, 0.f};
+}
+
+template <int EPI>
+__device__ __forceinline__ uint2 conv_aux(const ConvArgs &a, size_t o) {
+  if (EPI == EPI_ACT_SKIP || EPI == EPI_RAW_D || EPI == EPI_RAW_AND_D)
+    return *reinterpret_cast<const uint2 *>(a.aux + o);
+  return make_uint2(0u, 0u);
+}
+
+// (p, n: the position and its index; ls = log2 of the cells per sample)
 template <int EPI>
 __device__ __forceinline__ void conv_store(const ConvArgs &a, const Pos &p, long long n, int ls,
-                                           int co0, const floatx4 v) {
-  const size_t o = (size_t)n * a.cout_p + co0;
+                                           int co0, size_t o, const floatx4 v,
+                                           const floatx4 bias, const uint2 ax) {
   if (EPI == EPI_P) {
     if (co0 != 0) return;
     const int row = a.idx ? a.idx[p.b] : p.b;
     const float m = (float)p.z < a.thick[row] ? 1.f : 0.f;
     const long long r = n & ((1LL << ls) - 1);
-    for (int c = 0; c < 3; ++c) a.P[(((long long)p.b * 3 + c) << ls) + r] = m * (v[c] + a.bias[c]);
+    for (int c = 0; c < 3; ++c) a.P[(((long long)p.b * 3 + c) << ls) + r] = m * (v[c] + bias[c]);
     return;
   }
-  bf16_t r4[4], s4[4];
-  if (EPI == EPI_ACT || EPI == EPI_ACT_SKIP) {
-    for (int i = 0; i < 4; ++i) r4[i] = f2bf(act(v[i] + a.bias[co0 + i]));
-  } else {
-    for (int i = 0; i < 4; ++i) r4[i] = f2bf(v[i]);
-  }
+  float r[4];
+  for (int i = 0; i < 4; ++i)
+    r[i] = EPI == EPI_ACT || EPI == EPI_ACT_SKIP ? act(v[i] + bias[i]) : v[i];
+  const uint2 w0 = make_uint2(pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3]));
+  if (EPI != EPI_RAW_D) *reinterpret_cast<uint2 *>(a.out + o) = w0;
   if (EPI == EPI_ACT_SKIP || EPI == EPI_RAW_D || EPI == EPI_RAW_AND_D) {
-    const uint2 ax = *reinterpret_cast<const uint2 *>(a.aux + o);
     const bf16_t xa[4] = {(bf16_t)(ax.x & 0xFFFF), (bf16_t)(ax.x >> 16), (bf16_t)(ax.y & 0xFFFF),
                           (bf16_t)(ax.y >> 16)};
+    const bf16_t rr[4] = {(bf16_t)(w0.x & 0xFFFF), (bf16_t)(w0.x >> 16), (bf16_t)(w0.y & 0xFFFF),
+                          (bf16_t)(w0.y >> 16)};
+    float s[4];
     for (int i = 0; i < 4; ++i)
-      s4[i] = EPI == EPI_ACT_SKIP ? f2bf(bf2f(r4[i]) + bf2f(xa[i])) : f2bf(v[i] * act_slope(xa[i]));
+      s[i] = EPI == EPI_ACT_SKIP ? bf2f(rr[i]) + bf2f(xa[i]) : v[i] * act_slope(xa[i]);
+    const uint2 w1 = make_uint2(pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3]));
+    *reinterpret_cast<uint2 *>((EPI == EPI_RAW_D ? a.out : a.out2) + o) = w1;
   }
-  uint2 w0, w1;
-  w0.x = r4[0] | ((uint32_t)r4[1] << 16);
-  w0.y = r4[2] | ((uint32_t)r4[3] << 16);
-  w1.x = s4[0] | ((uint32_t)s4[1] << 16);
-  w1.y = s4[2] | ((uint32_t)s4[3] << 16);
-  if (EPI == EPI_RAW_D) {
-    *reinterpret_cast<uint2 *>(a.out + o) = w1;
-    return;
-  }
-  *reinterpret_cast<uint2 *>(a.out + o) = w0;
-  if (EPI == EPI_ACT_SKIP || EPI == EPI_RAW_AND_D) *reinterpret_cast<uint2 *>(a.out2 + o) = w1;
 }
 
 template <int MB, int NB, int EPI>
@@ -145,12 +173,11 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
   for (int mb = 0; mb < MB; ++mb)
     for (int j = 0; j < NB; ++j) acc[mb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  const bf16_t *wrow = a.w + (size_t)(co_blk + col) * kp;
   bf16x8 av[MB], bv[NB];
-  conv_operands<MB, NB>(a, wrow, kp, lc, 0, kq, p, inb, av, bv);
+  conv_operands<MB, NB>(a, co_blk, col, kp, lc, 0, kq, p, inb, av, bv);
   for (int k0 = 0; k0 < kp; k0 += 32) {
     bf16x8 an[MB], bn[NB];
-    if (k0 + 32 < kp) conv_operands<MB, NB>(a, wrow, kp, lc, k0 + 32, kq, p, inb, an, bn);
+    if (k0 + 32 < kp) conv_operands<MB, NB>(a, co_blk, col, kp, lc, k0 + 32, kq, p, inb, an, bn);
     for (int mb = 0; mb < MB; ++mb)
       for (int j = 0; j < NB; ++j)
         acc[mb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mb], bv[j], acc[mb][j], 0, 0, 0);
@@ -162,23 +189,45 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
   for (int j = 0; j < NB; ++j) {
     if (!inb[j]) continue;
     const long long n = nbase + 16 * j + col;
-    for (int mb = 0; mb < MB; ++mb)
-      conv_store<EPI>(a, p[j], n, ls, co_blk + mb * 16 + 4 * kq, acc[mb][j]);
+    for (int mb = 0; mb < MB; ++mb) {
+      const int co0 = co_blk + mb * 16 + 4 * kq;
+      const size_t o = (size_t)n * a.cout_p + co0;
+      conv_store<EPI>(a, p[j], n, ls, co0, o, acc[mb][j], conv_bias<EPI>(a, co0),
+                      conv_aux<EPI>(a, o));
+    }
   }
 }
 
 // LDS-tiled variant for grids with X >= 16, Y >= NR and Z >= 4: a
 // work-group owns a 4 x NR x 16 (z, y, x) block, wave w the NR rows of
-// plane w; per chunk of CC input channels the 6 x (NR + 2) x 18 input halo
-// of the block is staged in LDS once, and all 27 taps read their operand
-// from there.  MB * NR = 16 accumulator tiles per wave (NR >= 2).
+// plane w; per chunk of 16 input channels the 6 x (NR + 2) x 18 input halo
+// of the block is staged in LDS once (direct loads), and all 27 taps read their
+// operand from there, two taps of 16 channels per matrix step.  The next chunk's
+// halo lands in a second buffer while this chunk is multiplied.  A halo position is 32
+// bytes without padding: the 16 columns and the two halves of a tap cover 512
+// contiguous bytes, free of bank conflicts.
+// What bounds it: each step of a wave needs MB weight fragments (1 KB each,
+// from L1/L2) and NR input fragments (from LDS) for MB * NR matrix
+// instructions.  Plain weight rows put a fragment's 64 pieces of 16 bytes on 32
+// cache lines, and those lookups held the matrix cores at a quarter of their
+// rate; packed fragments (8 lines) do not.  Scheduling barriers keep the loads
+// ahead of the matrix instructions that hide them: left alone, the compiler
+// moved each down to its use and waited out its latency there.  The network's
+// twelve convolutions, 8 films of 64x64x16, width 32, forward: 814 -> 338 us
+// (257 -> 620 TFLOP/s of unpadded work), of which the packed weights alone gave
+// 814 -> 520; one film 585 -> 145 us.
 constexpr int HX = 18;
+__device__ const uint4 zero_piece = {0u, 0u, 0u, 0u};
 
-template <int MB, int NR, int CC, int EPI>
-__global__ __launch_bounds__(256) void k_conv_tile(ConvArgs a) {
-  constexpr int HY = NR + 2, HZ = 6, HPOS = HZ * HY * HX;
-  constexpr int LD = CC + 8;                       // LDS row stride (elements)
-  extern __shared__ bf16_t halo[];                 // [HPOS][LD]
+template <int MB, int NR, int EPI, bool PACKED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void k_conv_tile(ConvArgs a) {
+  constexpr int HY = NR + 2, HPOS = 6 * HY * HX;
+  constexpr int NS = (2 * HPOS + 255) / 256;       // 16-byte pieces per thread and chunk
+  constexpr int GR = NR < 4 ? NR : 4, NG = NR / GR;   // rows per group of input operands
+  constexpr int AHEAD = MB >= 4 ? 1 : 2;           // steps that the weights travel ahead
+  static_assert(NS <= 14, "one piece per step");
+  __shared__ __align__(16) bf16_t halo[2][HPOS * 16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int kq = lane >> 4, col = lane & 15;
   const int X = 1 << a.lx, Y = 1 << a.ly, Z = 1 << a.lz;
@@ -189,87 +238,185 @@ __global__ __launch_bounds__(256) void k_conv_tile(ConvArgs a) {
   const int z0 = (rem / (tx_n * ty_n)) * 4;
   rem %= tx_n * ty_n;
   const int y0 = (rem / tx_n) * NR, x0 = (rem % tx_n) * 16;
-  const int kp = 27 * a.cin_p;
   const int co_blk = blockIdx.y * MB * 16;
 
-  floatx4 acc[MB][NR];
-  for (int mb = 0; mb < MB; ++mb)
-    for (int j = 0; j < NR; ++j) acc[mb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const bf16_t *wrow = a.w + (size_t)(co_blk + col) * kp;
-
-  for (int ci0 = 0; ci0 < a.cin_p; ci0 += CC) {
-    for (int h = tid; h < HPOS * (CC / 8); h += 256) {
-      const int pos = h / (CC / 8), c8 = h % (CC / 8);
-      Pos hp;
-      hp.b = b;
-      hp.z = z0 - 1 + pos / (HY * HX);
-      hp.y = y0 - 1 + (pos / HX) % HY;
-      hp.x = x0 - 1 + pos % HX;
-      const long long src = gather_index(hp, 0, 0, 0, a.lx, a.ly, a.lz, a.in_up2);
-      uint4 v = make_uint4(0u, 0u, 0u, 0u);
-      if (src >= 0) v = *reinterpret_cast<const uint4 *>(a.in + src * a.cin_p + ci0 + 8 * c8);
-      *reinterpret_cast<uint4 *>(halo + pos * LD + 8 * c8) = v;
+  // input offsets of this thread's halo pieces, in 16-byte units from the
+  // first input plane of the halo (the launcher keeps them below 2^31); -1
+  // outside the grid
+  const int up = a.in_up2;
+  const int c8n = a.cin_p >> 3;
+  const int zb = (z0 > 0 ? z0 - 1 : 0) >> up;
+  const bf16_t *in = a.in + (((long long)b << (a.lz - up)) + zb) *
+                                ((long long)a.cin_p << (a.lx + a.ly - 2 * up));
+  int soff[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int h = tid + 256 * i, pos = h >> 1;
+    const int z = z0 - 1 + pos / (HY * HX), y = y0 - 1 + (pos / HX) % HY, x = x0 - 1 + pos % HX;
+    const bool ok = (unsigned)z < (unsigned)Z && (unsigned)y < (unsigned)Y &&
+                    (unsigned)x < (unsigned)X;
+    const int cell = ((((z >> up) - zb) << (a.ly - up)) + (y >> up)) * (X >> up) + (x >> up);
+    soff[i] = ok ? cell * c8n + (h & 1) : -1;
+  }
+  // piece i of chunk c of the halo into LDS buffer c & 1, by a direct load: the
+  // 64 pieces of a wave land side by side; those outside the grid come from
+  // zero_piece.  In assembly, because the compiler would wait for such a load
+  // before the next LDS read of any address; the wait before the barrier below
+  // is the one it needs.
+  auto stage = [&](int c, int i) {
+    if (tid + 256 * i < 2 * HPOS) {
+      const bf16_t *src = soff[i] >= 0 ? in + (size_t)(soff[i] + 2 * c) * 8
+                                       : reinterpret_cast<const bf16_t *>(&zero_piece);
+      const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) bf16_t *)
+          &halo[c & 1][(256 * i + 64 * wave) * 8];
+      asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                   :
+                   : "v"(src), "s"(__builtin_amdgcn_readfirstlane(at))
+                   : "memory", "m0");
     }
-    __syncthreads();
-    // K within the chunk: kk = tap * CC + c, steps of 32
-    for (int kk0 = 0; kk0 < 27 * CC; kk0 += 32) {
-      const int kk = kk0 + 8 * kq;
-      const bool kv = kk < 27 * CC;
-      const int t = kv ? kk / CC : 0, c = kk % CC;
-      const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;   // 0..2: halo offsets
-      bf16x8 av[MB];
-      for (int mb = 0; mb < MB; ++mb)
-        av[mb] = kv ? load8(wrow + (size_t)mb * 16 * kp + t * a.cin_p + ci0 + c) : zero8();
-      const bf16_t *hb = halo + (((wave + dz) * HY + dy) * HX + col + dx) * LD + c;
-      for (int j = 0; j < NR; ++j) {
-        const bf16x8 bv = kv ? *reinterpret_cast<const bf16x8 *>(hb + j * HX * LD) : zero8();
-        for (int mb = 0; mb < MB; ++mb)
-          acc[mb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mb], bv, acc[mb][j], 0, 0, 0);
+  };
+  const int kp = 27 * a.cin_p, co16 = a.cout_p >> 4;
+  const bf16_t *wl = PACKED ? a.w + (size_t)(co_blk >> 4) * 512 + lane * 8
+                            : a.w + (size_t)(co_blk + col) * kp + 8 * (kq & 1);
+  auto weights = [&](int c, int s, bf16x8 *av) {   // step s of chunk c
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      if (PACKED) {
+        av[mb] = load8(wl + ((size_t)(c * 14 + s) * co16 + mb) * 512);
+      } else {
+        const int t = 2 * s + (kq >> 1);
+        av[mb] = t < 27 ? load8(wl + (size_t)mb * 16 * kp + t * a.cin_p + 16 * c) : zero8();
       }
     }
+  };
+
+  floatx4 acc[MB][NR];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int j = 0; j < NR; ++j) acc[mb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int lb = (wave * HY * HX + col) * 16 + 8 * (kq & 1);
+  const bf16_t *hl = halo[0] + lb;                 // this lane's corner in the chunk's buffer
+  // input operands of rows GR g .. of step s, from LDS
+  auto inputs = [&](int s, int g, bf16x8 *bv) {
+    const int t0 = 2 * s, t1 = s < 13 ? 2 * s + 1 : t0;
+    const int o0 = ((t0 / 9) * HY + t0 / 3 % 3) * HX + t0 % 3;
+    const int o1 = ((t1 / 9) * HY + t1 / 3 % 3) * HX + t1 % 3;
+    const bf16_t *hb = hl + (kq >= 2 ? o1 : o0) * 16;
+#pragma unroll
+    for (int j = 0; j < GR; ++j)
+      bv[j] = *reinterpret_cast<const bf16x8 *>(hb + (GR * g + j) * HX * 16);
+  };
+  const int chunks = a.cin_p >> 4;
+  bf16x8 w0[MB], w1[MB], w2[MB], bv[2][GR];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) stage(0, i);
+  weights(0, 0, w0);
+  if (AHEAD == 2) weights(0, 1, w1);
+  for (int c = 0; c < chunks; ++c) {
+    // this wave's part of the chunk has landed, then everyone's
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    hl = halo[c & 1] + lb;
+    inputs(0, 0, bv[0]);
+    // weights travel AHEAD steps ahead and inputs one group of rows; the
+    // scheduling barriers keep the compiler from moving the loads down to
+    // their uses
+#pragma unroll
+    for (int s = 0; s < 14; ++s) {
+      if (s < NS && c + 1 < chunks) stage(c + 1, s);   // over the chunk before this one
+      if (s < 14 - AHEAD) weights(c, s + AHEAD, AHEAD == 1 ? w1 : w2);
+      else if (c + 1 < chunks) weights(c + 1, s + AHEAD - 14, AHEAD == 1 ? w1 : w2);
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        bf16x8 *now = bv[(s * NG + g) & 1], *next = bv[(s * NG + g + 1) & 1];
+        if (g + 1 < NG) inputs(s, g + 1, next);
+        else if (s < 13) inputs(s + 1, 0, next);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < GR; ++j) {
+          if (s == 13 && kq >= 2) now[j] = zero8();    // the half step behind tap 26
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+            acc[mb][GR * g + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                w0[mb], now[j], acc[mb][GR * g + j], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        w0[mb] = w1[mb];
+        if (AHEAD == 2) w1[mb] = w2[mb];
+      }
+    }
   }
 
   const int ls = a.lx + a.ly + a.lz;
+  const long long n0 =
+      ((((long long)b << a.lz) + z0 + wave) * Y + y0) * (long long)X + x0 + col;
+  const size_t o0 = (size_t)n0 * a.cout_p + co_blk + 4 * kq, row = (size_t)X * a.cout_p;
+  floatx4 bias[MB];                                // every load before the first store
+  uint2 ax[MB][NR];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    bias[mb] = conv_bias<EPI>(a, co_blk + mb * 16 + 4 * kq);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) ax[mb][j] = conv_aux<EPI>(a, o0 + j * row + mb * 16);
+  }
+#pragma unroll
   for (int j = 0; j < NR; ++j) {
-    Pos pj;
-    pj.b = b;
-    pj.z = z0 + wave;
-    pj.y = y0 + j;
-    pj.x = x0 + col;
-    const long long n = ((((long long)b << a.lz) + pj.z) * Y + pj.y) * (long long)X + pj.x;
+    const Pos pj = {b, z0 + wave, y0 + j, x0 + col};
+#pragma unroll
     for (int mb = 0; mb < MB; ++mb)
-      conv_store<EPI>(a, pj, n, ls, co_blk + mb * 16 + 4 * kq, acc[mb][j]);
+      conv_store<EPI>(a, pj, n0 + (long long)j * X, ls, co_blk + mb * 16 + 4 * kq,
+                      o0 + j * row + mb * 16, acc[mb][j], bias[mb], ax[mb][j]);
   }
 }
 
-template <int MB, int EPI>
-static hipError_t conv_tile(const ConvArgs &a, dim3 grid, hipStream_t s) {
-  // rows per wave NR = 16 / MB (2..8); channel chunk of 16 per halo load:
-  // 6 x (NR + 2) x 18 positions x 24 elements x 2 B (<= 52 KB)
-  constexpr int NR = MB >= 8 ? 2 : 16 / MB > 8 ? 8 : 16 / MB;
-  const size_t shm = (size_t)6 * (NR + 2) * HX * 24 * 2;
-  hipLaunchKernelGGL((k_conv_tile<MB, NR, 16, EPI>), grid, dim3(256), shm, s, a);
+template <int MB, int NR, int EPI>
+static hipError_t conv_tile(const ConvArgs &a, hipStream_t s) {
+  const long long blocks = ((long long)a.nb << (a.lx + a.ly + a.lz)) / (64 * NR);
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks, a.cout_p / (16 * MB), 1);
+  if (a.packed) hipLaunchKernelGGL((k_conv_tile<MB, NR, EPI, true>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_conv_tile<MB, NR, EPI, false>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
+}
+
+// Tile of the LDS kernel: MB * NR accumulator tiles per wave, the most (16)
+// that still give TILE_GROUPS work-groups; smaller ones leave the matrix cores
+// more often idle but fill the chip on small grids and batches: with 64 groups
+// of 16 tiles, the 128-channel layers of 8 films (16x16x4) took 112 us each, with
+// 256 groups of 4 tiles 20 us.  The order of every sum is the same in all of
+// them, and in plain and packed weights.
+constexpr long long TILE_GROUPS = 512;
+
+template <int EPI>
+static hipError_t conv_pick(const ConvArgs &a, long long npos, hipStream_t s) {
+  const int co16 = a.cout_p / 16, Y = 1 << a.ly;
+  auto fits = [&](int mb, int nr) {
+    return mb <= co16 && Y >= nr && npos / (64 * nr) * (co16 / mb) >= TILE_GROUPS;
+  };
+  if (EPI == EPI_P || co16 == 1) {
+    if (fits(1, 8)) return conv_tile<1, 8, EPI>(a, s);
+    return conv_tile<1, 2, EPI>(a, s);
+  }
+  if constexpr (EPI != EPI_P) {
+    if (co16 == 2 && fits(2, 8)) return conv_tile<2, 8, EPI>(a, s);
+    if (fits(4, 4)) return conv_tile<4, 4, EPI>(a, s);
+    if (fits(2, 4)) return conv_tile<2, 4, EPI>(a, s);
+    return conv_tile<2, 2, EPI>(a, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 // positions per wave: 16 * NB with MB * NB = 16 accumulator tiles (NB >= 2)
 template <int EPI>
 static hipError_t conv_mb(const ConvArgs &a, long long npos, hipStream_t s) {
+  // (the input offsets of a halo fit 31 bits)
+  if (a.lx >= 4 && a.ly >= 1 && a.lz >= 2 &&
+      ((6LL * (a.cin_p / 8)) << (a.lx + a.ly)) < (1LL << 31))
+    return conv_pick<EPI>(a, npos, s);
   const int mb = a.cout_p / 16 >= 8 ? 8 : a.cout_p / 16;
-  const int nr = mb >= 8 ? 2 : 16 / mb > 8 ? 8 : 16 / mb;
-  if (a.lx >= 4 && (1 << a.ly) >= nr && a.lz >= 2) {
-    const long long blocks = npos / (64LL * nr);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    dim3 grid((unsigned)blocks, a.cout_p / (16 * mb), 1);
-    switch (mb) {
-      case 1: return conv_tile<1, EPI>(a, grid, s);
-      case 2: return conv_tile<2, EPI>(a, grid, s);
-      case 4: return conv_tile<4, EPI>(a, grid, s);
-      case 8: return conv_tile<8, EPI>(a, grid, s);
-      default: return hipErrorInvalidValue;
-    }
-  }
   const int nbk = mb >= 8 ? 2 : 16 / mb > 8 ? 8 : 16 / mb;
   const long long blocks = (npos + 64 * nbk - 1) / (64 * nbk);
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -608,6 +755,14 @@ hipError_t launch_up_bwd(const bf16_t *g, const bf16_t *a, int lx, int ly, int l
   return hipGetLastError();
 }
 
+// the same rounding in integers: behind a conversion from double the compiler
+// would round once to BF16, not first to float as the network's definition has it
+__device__ inline bf16_t f2bf_float(float f) {
+  uint32_t u = __float_as_uint(f);
+  u += 0x7FFFu + ((u >> 16) & 1u);
+  return (bf16_t)(u >> 16);
+}
+
 // squared error of P against the target rows over the film cells, divided by
 // 3 x the film cells of the batch (FP64 partial per block), and the BF16
 // gradient 2 m (P - target) / count in channels 0..2 of 16
@@ -647,7 +802,8 @@ __global__ __launch_bounds__(256) void k_loss(const float *P, const float *targe
       g[c] = (float)(m * 2.0 * d * inv_count);
     }
     uint32_t w[8];
-    for (int i = 0; i < 8; ++i) w[i] = f2bf(g[2 * i]) | ((uint32_t)f2bf(g[2 * i + 1]) << 16);
+    for (int i = 0; i < 8; ++i)
+      w[i] = f2bf_float(g[2 * i]) | ((uint32_t)f2bf_float(g[2 * i + 1]) << 16);
     uint4 *o = reinterpret_cast<uint4 *>(gy + n * 16);
     o[0] = make_uint4(w[0], w[1], w[2], w[3]);
     o[1] = make_uint4(w[4], w[5], w[6], w[7]);
@@ -739,20 +895,26 @@ hipError_t launch_adam(float *master, float *m, float *v, const float *grad, lon
   return hipGetLastError();
 }
 
-// FP32 master (one layer, public order) -> BF16 forward [cout_p][27 cin_p],
-// mirrored backward-data copy [cin_p][27 cout_p] and the padded FP32 bias
+// FP32 master (one layer, public order) -> packed BF16 forward weights (rows
+// cout, channels cin), packed backward-data copy (rows cin, channels cout, tap
+// mirrored) and the padded FP32 bias
 __global__ void k_cast_weights(const float *master, int cin, int cout, int cin_p, int cout_p,
                                bf16_t *w, bf16_t *wt, float *bias) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long nw = (long long)cout_p * 27 * cin_p;
+  const long long nw = 28LL * cin_p * cout_p;
   if (i < nw) {
-    const int ci = (int)(i % cin_p);
-    const int t = (int)((i / cin_p) % 27);
-    const int co = (int)(i / (27LL * cin_p));
-    const float val = (co < cout && ci < cin) ? master[((long long)co * 27 + t) * cin + ci] : 0.f;
-    const bf16_t h = f2bf(val);
-    w[i] = h;
-    wt[((size_t)ci * 27 + (26 - t)) * cout_p + co] = h;
+    const int k8 = (int)(i & 7), col = (int)(i >> 3) & 15, kq = (int)(i >> 7) & 3;
+    const int frag = (int)(i >> 9);
+    // (chunk, step, row block) of this element for 16-row blocks rows / 16
+    auto value = [&](int rows16, bool mirror) -> bf16_t {
+      const int m = frag % rows16, s = frag / rows16 % 14, c = frag / (14 * rows16);
+      const int t = 2 * s + (kq >> 1), row = 16 * m + col, ch = 16 * c + 8 * (kq & 1) + k8;
+      const int co = mirror ? ch : row, ci = mirror ? row : ch, tap = mirror ? 26 - t : t;
+      const bool in = t < 27 && co < cout && ci < cin;
+      return f2bf(in ? master[((long long)co * 27 + tap) * cin + ci] : 0.f);
+    };
+    w[i] = value(cout_p >> 4, false);
+    wt[i] = value(cin_p >> 4, true);
   } else if (i < nw + cout_p) {
     const int co = (int)(i - nw);
     bias[co] = co < cout ? master[(long long)cout * 27 * cin + co] : 0.f;
@@ -761,7 +923,7 @@ __global__ void k_cast_weights(const float *master, int cin, int cout, int cin_p
 
 hipError_t launch_cast_weights(const float *master, int cin, int cout, int cin_p, int cout_p,
                                bf16_t *w, bf16_t *wt, float *bias, hipStream_t s) {
-  const long long n = (long long)cout_p * 27 * cin_p + cout_p;
+  const long long n = (long long)packed_size(cin_p, cout_p) + cout_p;
   hipLaunchKernelGGL(k_cast_weights, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, master,
                      cin, cout, cin_p, cout_p, w, wt, bias);
   return hipGetLastError();

@@ -103,6 +103,7 @@ hipError_t conv_fwd(tdgl_net *n, int l, int nb, const bf16_t *in, int epi, bf16_
   ConvArgs a{};
   a.in = in;
   a.w = Ly.w;
+  a.packed = 1;
   a.bias = Ly.bias;
   a.out = out;
   a.out2 = out2;
@@ -127,6 +128,7 @@ hipError_t conv_bwd(tdgl_net *n, int l, int nb, const bf16_t *g, int epi, bf16_t
   ConvArgs a{};
   a.in = g;
   a.w = Ly.wt;
+  a.packed = 1;
   a.out = out;
   a.out2 = out2;
   a.aux = aux;
@@ -298,7 +300,7 @@ tdgl_status tdgl_net_create(const tdgl_net_cfg *cfg, void *hip_stream, tdgl_net 
             alloc(n, &n->mom2, n->nparam) && alloc(n, &n->grad, n->nparam);
   for (int l = 0; ok && l < NLAYER; ++l) {
     Layer &Ly = n->L[l];
-    const size_t nw = (size_t)Ly.cout_p * 27 * Ly.cin_p;
+    const size_t nw = packed_size(Ly.cin_p, Ly.cout_p);
     ok = alloc(n, &Ly.w, nw) && alloc(n, &Ly.wt, nw) && alloc(n, &Ly.bias, (size_t)Ly.cout_p);
   }
   ok = ok && alloc(n, &n->x0, c0 * 16) && alloc(n, &n->e0a, c0 * w0) && alloc(n, &n->e0, c0 * w0) &&

@@ -4,9 +4,13 @@
 // Tensors are BF16 (stored as uint16), channels-last: [position][channel],
 // position = ((b * Z + z) * Y + y) * X + x, the channel count padded to a
 // multiple of 16.  Grid sizes are powers of two (log2 in lx, ly, lz).
-// Weights: forward [cout_p][27 * cin_p] (k = tap * cin_p + ci), the
-// backward-data copy [cin_p][27 * cout_p] with the tap mirrored; tap
-// t = 9 (dz + 1) + 3 (dy + 1) + (dx + 1).
+// Weights: plain, [cout_p][27 * cin_p] (k = tap * cin_p + ci; tap t =
+// 9 (dz + 1) + 3 (dy + 1) + (dx + 1)), as the single-layer entry points take
+// them, or packed in the order of the matrix operands, as the network keeps
+// its forward weights and the backward-data copy (channels exchanged, tap
+// mirrored): for every chunk c of 16 input channels and step s = 0..13 the
+// 16-row blocks m as 64 lanes x 8 values, lane (kq, col) holding row 16 m + col,
+// tap 2 s + kq / 2 (zero for tap 27), channels 16 c + 8 (kq % 2) + 0..7.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstddef>
@@ -30,7 +34,8 @@ enum ConvEpi {
 
 struct ConvArgs {
   const bf16_t *in;   // input tensor, cin_p channels (half resolution if in_up2)
-  const bf16_t *w;    // [cout_p][27 * cin_p]
+  const bf16_t *w;    // plain or packed weights of cout_p rows, cin_p channels
+  int packed;
   const float *bias;  // [cout_p] or null
   bf16_t *out, *out2; // [n][cout_p]
   const bf16_t *aux;  // [n][cout_p]: skip addend or activation
@@ -41,6 +46,8 @@ struct ConvArgs {
   int lx, ly, lz, nb; // output grid (log2) and samples
   int cin_p, cout_p;
 };
+
+constexpr size_t packed_size(int cin_p, int cout_p) { return (size_t)28 * cin_p * cout_p; }
 
 struct WgradArgs {
   const bf16_t *g;    // [n][cout_p] gradient of the layer output (pre-activation)
