@@ -155,7 +155,7 @@ hipError_t wgrad(tdgl_net *n, int l, int nb, const bf16_t *g, const bf16_t *in) 
   a.nb = nb;
   a.cin_p = Ly.cin_p;
   a.cout_p = Ly.cout_p;
-  wgrad_split((long long)nb * n->cells(Ly.level), 27 * Ly.cin_p, &a.splits, &a.chunk);
+  wgrad_plan(&a);
   hipError_t e = launch_wgrad(a, n->s);
   if (e != hipSuccess) return e;
   return launch_reduce_grad(n->part, n->bpart, a.splits, Ly.cin, Ly.cout, Ly.cin_p, Ly.cout_p,
@@ -319,10 +319,16 @@ tdgl_status tdgl_net_create(const tdgl_net_cfg *cfg, void *hip_stream, tdgl_net 
   size_t part = 0, bpart = 0;
   for (int l = 0; l < NLAYER; ++l) {
     const Layer &Ly = n->L[l];
-    int sp, ch;
-    wgrad_split((long long)B * n->cells(Ly.level), 27 * Ly.cin_p, &sp, &ch);
-    part = std::max(part, (size_t)sp * Ly.cout_p * 27 * Ly.cin_p);
-    bpart = std::max(bpart, (size_t)sp * Ly.cout_p);
+    WgradArgs a{};
+    a.lx = n->lvx(Ly.level);
+    a.ly = n->lvy(Ly.level);
+    a.lz = n->lvz(Ly.level);
+    a.nb = (int)B;
+    a.cin_p = Ly.cin_p;
+    a.cout_p = Ly.cout_p;
+    wgrad_plan(&a);
+    part = std::max(part, (size_t)a.max_splits * Ly.cout_p * 27 * Ly.cin_p);
+    bpart = std::max(bpart, (size_t)a.max_splits * Ly.cout_p);
   }
   const size_t lp = (c0 + 255) / 256;
   ok = ok && alloc(n, &n->part, part) && alloc(n, &n->bpart, bpart) &&
@@ -512,7 +518,7 @@ tdgl_status tdgl_net_profile(tdgl_net *n, int nb, const float *T, const float *t
       a.nb = nb;
       a.cin_p = Ly.cin_p;
       a.cout_p = Ly.cout_p;
-      wgrad_split((long long)nb * n->cells(Ly.level), 27 * Ly.cin_p, &a.splits, &a.chunk);
+      wgrad_plan(&a);
       CK(launch_wgrad(a, n->s));
     }
     CK(hipEventRecord(ev[3], n->s));
@@ -575,9 +581,15 @@ tdgl_status tdgl_nn_wgrad_workspace(int nb, int lx, int ly, int lz, int cin_p, i
   if (!bytes || nb < 1 || lx < 0 || ly < 0 || lz < 0 || lx > 12 || ly > 12 || lz > 12 ||
       !pow2(cin_p) || cin_p < 16 || !pow2(cout_p) || cout_p < 16)
     return TDGL_E_ARG;
-  int sp, ch;
-  wgrad_split((long long)nb << (lx + ly + lz), 27 * cin_p, &sp, &ch);
-  *bytes = ((size_t)sp * cout_p * 27 * cin_p + (size_t)sp * cout_p) * sizeof(float);
+  WgradArgs a{};
+  a.lx = lx;
+  a.ly = ly;
+  a.lz = lz;
+  a.nb = nb;
+  a.cin_p = cin_p;
+  a.cout_p = cout_p;
+  wgrad_plan(&a);
+  *bytes = (size_t)a.splits * cout_p * (27 * (size_t)cin_p + 1) * sizeof(float);
   return TDGL_OK;
 }
 
@@ -598,7 +610,7 @@ tdgl_status tdgl_nn_conv3_wgrad(const void *g, const void *in, int in_up2, int n
   a.nb = nb;
   a.cin_p = cin_p;
   a.cout_p = cout_p;
-  wgrad_split((long long)nb << (lx + ly + lz), 27 * cin_p, &a.splits, &a.chunk);
+  wgrad_plan(&a);
   a.part = static_cast<float *>(workspace);
   a.bpart = a.part + (size_t)a.splits * cout_p * 27 * cin_p;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);

@@ -57,12 +57,15 @@ struct WgradArgs {
   int in_up2;
   int lx, ly, lz, nb;
   int cin_p, cout_p;
-  int splits, chunk;  // positions per split (multiple of 32)
+  // from wgrad_plan: the kernel, the splits, and per split the tiles (tiled) or
+  // the positions, a multiple of 32
+  int tiled, splits, chunk;
+  int max_splits;     // no smaller batch of this layer has more splits
 };
 
 hipError_t launch_conv(int epi, const ConvArgs &a, hipStream_t s);
 hipError_t launch_wgrad(const WgradArgs &a, hipStream_t s);
-void wgrad_split(long long npos, int kp, int *splits, int *chunk);
+void wgrad_plan(WgradArgs *a);    // from the grid and the channels
 
 // elementwise parts
 // ops: per-sample in-plane symmetry op (bits: 1 mirror x, 2 mirror y, 4 swap
