@@ -215,8 +215,10 @@ tdgl_status tdgl_set_terms(tdgl_ctx *ctx, unsigned mask);
  * tdgl_autotune restart it (the next two steps are Heun steps).
  * TDGL_RK45: the adaptive Dormand-Prince 5(4) pair, seven field evaluations
  * per attempt; dtau is the first trial step, tdgl_step(n) makes n accepted
- * steps (see tdgl_set_rk_tolerances); RK45 steps are launched eagerly and
- * synchronise once per attempt.  This call resets the RK45 time and step. */
+ * steps (see tdgl_set_rk_tolerances); the step size and the decision on an
+ * attempt stay on the device, and tdgl_step synchronises once per 64 steps and
+ * once more for each group of rejections.  This call resets the RK45 time and
+ * step. */
 tdgl_status tdgl_set_integrator(tdgl_ctx *ctx, int scheme, double dtau);
 
 /* RK45 error control: an attempt is accepted when, over every cell and

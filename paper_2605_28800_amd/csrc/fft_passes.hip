@@ -45,6 +45,7 @@ __global__ void k_fx(const T *__restrict__ in, long long nrows, int n_in, long l
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T> *lds = reinterpret_cast<cpx<T> *>(smem_raw);
     cpx<T> *stg = lds + lpw * LEN;                  // [M2 + 1][lpw] output staging
+    if (fz.flag && fz.nb == 1 && fz.flag[0]) return;       // nothing to do for any row
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int l = tid / TPL, t = tid - l * TPL;
     const long long r0 = (long long)blockIdx.x * lpw;

@@ -105,11 +105,32 @@ struct UpdArgs {
     const void *hist_b;    // STEP_MS stage 2: E_{n-2}; stage 3: E_{n-1}
     const void *rk_base;   // STEP_RK: P_n
     void *rk_k;            // STEP_RK: k_1..k_7, each [nb][3][nz][ny][nx]
-    double rk_h;           // STEP_RK: step size
-    double rk_atol, rk_rtol;
+    const struct RkState *rk;   // STEP_RK: step size and tolerances
     const void *cross;     // field of the gradient cross terms (k_cross), or null
     unsigned mgx, mnz;     // magic numbers of the launch's grid divisions (set by the launcher)
 };
+
+// The RK45 controller's state on the device.  An attempt (seven stages) is
+// followed by k_rk_control, which reduces the error estimate and either accepts
+// (the new state is copied over P_n) or rejects (the x spectra of P_n are made
+// again), so that attempts follow each other without the host; once `target`
+// steps are accepted, or a failure ends the run, every instance is frozen and
+// the attempts still enqueued do nothing.
+struct RkState {
+    double h, tau;                       // step size; reduced time of the accepted steps
+    double atol, rtol;
+    long long accepted, rejected, target;
+    int row;                             // rejections in a row
+    int fail;                            // 1: error estimate not finite, 2: 64 in a row
+    int keep;                            // k_rk_copy: the attempt was not accepted
+    int spectra;                         // k_fx: the spectra need no remaking
+    int stop[1];                         // frozen flags, one per instance
+};
+hipError_t launch_rk_begin(RkState *r, int nb, double h, double atol, double rtol,
+                           long long target, hipStream_t s);
+hipError_t launch_rk_control(RkState *r, int nb, const double *partials, int n, hipStream_t s);
+hipError_t launch_rk_copy(const RkState *r, const void *src, void *dst, size_t bytes,
+                          hipStream_t s);
 
 // field of the cross terms of the gradient energy (G12, G44 - G44') of P
 hipError_t launch_cross(int prec, const Geom &g, const void *P, void *H, const void *coef,

@@ -25,46 +25,11 @@
 // yt rows of a group read and write yt*KB contiguous values per block.
 #include <mutex>
 
+#include "cell.h"
 #include "fft_core.h"
 #include "internal.h"
 
 namespace tdgl {
-
-template <typename T>
-__device__ __forceinline__ T landau_dfdp(const T p[3], const T sq[3], const T *cf, int i)
-{
-    const int j = i == 0 ? 1 : 0;
-    const int k = i == 2 ? 1 : 2;
-    const T sj = sq[j] + sq[k];
-    const T s4 = sq[j] * sq[j] + sq[k] * sq[k];
-    // d/dP_i of eq 3 (cf: a1x a1y a1z a11 a12 a111 a112 a123)
-    return p[i] * (T(2) * cf[i] + T(4) * cf[3] * sq[i] + T(2) * cf[4] * sj +
-                   T(6) * cf[5] * sq[i] * sq[i] + cf[6] * (T(4) * sq[i] * sj + T(2) * s4) +
-                   T(2) * cf[7] * sq[j] * sq[k]);
-}
-
-template <typename T>
-__device__ __forceinline__ T landau_f(const T sq[3], const T *cf)
-{
-    const T x = sq[0], y = sq[1], z = sq[2];
-    return cf[0] * x + cf[1] * y + cf[2] * z + cf[3] * (x * x + y * y + z * z) +
-           cf[4] * (x * y + y * z + z * x) + cf[5] * (x * x * x + y * y * y + z * z * z) +
-           cf[6] * (x * x * (y + z) + y * y * (x + z) + z * z * (x + y)) + cf[7] * x * y * z;
-}
-
-// Dormand-Prince 5(4) tableau (Dormand & Prince 1980): row s of RK_A gives
-// the weights of k_1..k_s for the stage point s + 1 (row 6 is the
-// fifth-order solution); RK_E = fifth- minus fourth-order weights.
-__constant__ double RK_A[6][6] = {
-    {1.0 / 5, 0, 0, 0, 0, 0},
-    {3.0 / 40, 9.0 / 40, 0, 0, 0, 0},
-    {44.0 / 45, -56.0 / 15, 32.0 / 9, 0, 0, 0},
-    {19372.0 / 6561, -25360.0 / 2187, 64448.0 / 6561, -212.0 / 729, 0, 0},
-    {9017.0 / 3168, -355.0 / 33, 46732.0 / 5247, 49.0 / 176, -5103.0 / 18656, 0},
-    {35.0 / 384, 0, 500.0 / 1113, 125.0 / 192, -2187.0 / 6784, 11.0 / 84}};
-__constant__ double RK_E[7] = {35.0 / 384 - 5179.0 / 57600, 0, 500.0 / 1113 - 7571.0 / 16695,
-                               125.0 / 192 - 393.0 / 640, -2187.0 / 6784 + 92097.0 / 339200,
-                               11.0 / 84 - 187.0 / 2100, -1.0 / 40};
 
 // Cross terms of the gradient energy (G12 P_i,i P_j,j and (G44 - G44')
 // P_i,j P_j,i) for one cell, with cell-centred central differences in which
@@ -165,6 +130,9 @@ __global__ void __launch_bounds__(UpdMaxThreads<T>::v)
             }
             return;
         }
+    }
+    if constexpr (MODE == UPD_STEP_RK) {
+        if (g.frozen && g.frozen[b]) return;      // the run is over (RkState)
     }
     // LDS: rows hs[(c*yt + yy)*HS + x] (HS = nx + 2 rounded down to even, so
     // that (even, odd) sample pairs are aligned as one complex value), then
@@ -470,7 +438,7 @@ __global__ void __launch_bounds__(UpdMaxThreads<T>::v)
                 const long long ho = 3LL * b * comp + off;
                 T *K = reinterpret_cast<T *>(a.rk_k);
                 const T *Pn = reinterpret_cast<const T *>(a.rk_base);
-                const T h = (T)a.rk_h;
+                const T h = (T)a.rk->h;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     const T e = material ? E[c] : T(0);
@@ -485,8 +453,8 @@ __global__ void __launch_bounds__(UpdMaxThreads<T>::v)
                         T acc = T(RK_E[6]) * e;
                         for (int j = 0; j < 6; ++j)
                             acc += T(RK_E[j]) * K[j * ko + c * comp + ho];
-                        const T sc = T(a.rk_atol) +
-                                     T(a.rk_rtol) * (fabs(pn) > fabs(p[c]) ? fabs(pn) : fabs(p[c]));
+                        const T sc = T(a.rk->atol) +
+                                     T(a.rk->rtol) * (fabs(pn) > fabs(p[c]) ? fabs(pn) : fabs(p[c]));
                         const T r = fabs(h * acc) / sc;
                         rkerr = r > rkerr ? r : rkerr;
                         o[c] = p[c];                             // P5 itself (for the spectrum)
@@ -1005,6 +973,106 @@ hipError_t launch_relax_test(const double *E, const RelaxState &r, int nb, bool 
 {
     hipLaunchKernelGGL(k_relax_test, dim3(1), dim3(256), 0, s, E, r, nb, init ? 1 : 0, check,
                        rtol, floor, retire ? 1 : 0);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------ RK45 control
+__global__ void k_rk_begin(RkState *r, int nb, double h, double atol, double rtol,
+                           long long target)
+{
+    for (int b = threadIdx.x; b < nb; b += blockDim.x) r->stop[b] = 0;
+    if (threadIdx.x == 0) {
+        r->h = h;
+        r->tau = 0.0;
+        r->atol = atol;
+        r->rtol = rtol;
+        r->accepted = r->rejected = 0;
+        r->target = target;
+        r->row = r->fail = 0;
+        r->keep = r->spectra = 1;
+    }
+}
+
+// The decision on one attempt from the scaled error maxima of its n groups
+// (partials[8 i]); accepted if the largest is at most 1.  One work-group.
+__global__ void k_rk_control(RkState *r, int nb, const double *__restrict__ partials, int n)
+{
+    __shared__ double red[256];
+    __shared__ int over;
+    const int tid = threadIdx.x;
+    if (tid == 0) {
+        over = r->stop[0];
+        r->keep = r->spectra = 1;
+    }
+    __syncthreads();
+    if (over) return;
+    double e = 0.0;
+    for (int i = tid; i < n; i += 256) {
+        const double v = partials[(long long)i * 8];
+        e = v > e ? v : e;
+    }
+    red[tid] = e;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (tid < w && red[tid + w] > red[tid]) red[tid] = red[tid + w];
+        __syncthreads();
+    }
+    if (tid == 0) {
+        const double err = red[0];
+        const double fac = err > 0.0 ? 0.9 * pow(err, -0.2) : 5.0;
+        if (!isfinite(err)) {
+            r->fail = 1;
+        } else if (err <= 1.0) {
+            r->tau += r->h;
+            r->h *= fac < 0.2 ? 0.2 : (fac > 5.0 ? 5.0 : fac);
+            ++r->accepted;
+            r->row = 0;
+            r->keep = 0;
+        } else {
+            r->h *= fac < 0.2 ? 0.2 : fac;
+            ++r->rejected;
+            r->spectra = 0;
+            if (++r->row == 64) r->fail = 2;
+        }
+        over = r->fail != 0 || r->accepted == r->target;
+    }
+    __syncthreads();
+    if (over)
+        for (int b = tid; b < nb; b += 256) r->stop[b] = 1;
+}
+
+__global__ void k_rk_copy(const RkState *r, const uint2 *__restrict__ src, uint2 *__restrict__ dst,
+                          size_t n8, const unsigned *__restrict__ tail_src, unsigned *tail_dst)
+{
+    if (r->keep) return;
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = i0; i < n8; i += (size_t)gridDim.x * blockDim.x) dst[i] = src[i];
+    if (i0 == 0 && tail_dst) *tail_dst = *tail_src;       // an odd number of floats
+}
+
+hipError_t launch_rk_begin(RkState *r, int nb, double h, double atol, double rtol,
+                           long long target, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_rk_begin, dim3(1), dim3(256), 0, s, r, nb, h, atol, rtol, target);
+    return hipGetLastError();
+}
+
+hipError_t launch_rk_control(RkState *r, int nb, const double *partials, int n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_rk_control, dim3(1), dim3(256), 0, s, r, nb, partials, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_rk_copy(const RkState *r, const void *src, void *dst, size_t bytes,
+                          hipStream_t s)
+{
+    const size_t n8 = bytes / 8;
+    const size_t blocks = (n8 + 255) / 256;
+    const bool tail = (bytes & 4) != 0;
+    hipLaunchKernelGGL(k_rk_copy, dim3((unsigned)(blocks < 1 ? 1 : (blocks < 2048 ? blocks : 2048))),
+                       dim3(256), 0, s, r, (const uint2 *)src, (uint2 *)dst, n8,
+                       tail ? (const unsigned *)src + 2 * n8 : nullptr,
+                       tail ? (unsigned *)dst + 2 * n8 : nullptr);
     return hipGetLastError();
 }
 
