@@ -13,7 +13,7 @@
 // W_{PR}^{rk}, R-point DFT, outputs to y[(i-k) R + k + r P].  The first stage
 // (P = 1) needs no twiddles and reads the registers; the last stage
 // (P R = M) writes y[i + r M/R], which is again the register layout.
-// Radices: 8, 4, 2 for powers of two; 4, 2 and a last 3 otherwise.
+// Radices: 8, 4, 2 for powers of two; 4, 2 and a last 12 otherwise.
 //
 // Forward transforms use W = exp(-2 pi i/M); inverse transforms the
 // conjugate, unnormalised.
@@ -172,12 +172,34 @@ __device__ __forceinline__ void dft3(cpx<T> *v)
     v[2] = csub(m, r);
 }
 
+// 12-point DFT by the prime-factor map (3 and 4 are coprime): with n = 4 a + 3 b
+// and k = 4 p + 9 q (mod 12), n k = 4 a p + 3 b q (mod 12), so four 3-point and
+// three 4-point DFTs without twiddles.
+template <typename T, bool INV>
+__device__ __forceinline__ void dft12(cpx<T> *v)
+{
+    cpx<T> u[3][4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        cpx<T> w[3] = {v[(3 * b) % 12], v[(4 + 3 * b) % 12], v[(8 + 3 * b) % 12]};
+        dft3<T, INV>(w);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) u[p][b] = w[p];
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        dft4<T, INV>(u[p]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[(4 * p + 9 * q) % 12] = u[p][q];
+    }
+}
+
 template <typename T, int R, bool INV>
 __device__ __forceinline__ void dftR(cpx<T> *v)
 {
-    if constexpr (R == 8) dft8<T, INV>(v);
+    if constexpr (R == 12) dft12<T, INV>(v);
+    else if constexpr (R == 8) dft8<T, INV>(v);
     else if constexpr (R == 4) dft4<T, INV>(v);
-    else if constexpr (R == 3) dft3<T, INV>(v);
     else dft2<T, INV>(v);
 }
 
@@ -213,9 +235,12 @@ struct LinePad {
 
 // Stockham plan of a line of M points.  M = 2^a: eight points per thread,
 // radix 8 while at least 8 points remain, then 4 or 2.  M = 3 * 2^a (a >= 2):
-// twelve points per thread, radix 4 while a multiple of 12 remains, one
-// radix 2 where 6 remain, and a last radix-3 stage, so that every stage
-// before the last has a power-of-two span P.
+// twelve points per thread, radix 4 while 48 or more remain, one radix 2
+// where 24 remain, and a last radix-12 stage in registers, so that every stage
+// before the last has a power-of-two span P.  (Radices 4, 2 and a last 3 take
+// one more exchange through LDS for every length: Heun steps of 48x40x12 45.5 us
+// against 41.6 FP32, 54.1 / 50.7 FP64; of 190x180x20 225 / 208 and 386 / 365; of 16
+// boxes of 96x96x8 FP32 223 / 219; only 10x11x6 is no faster, 35.5 / 36.0 FP64.)
 template <int M>
 struct Plan {
     static constexpr bool R3 = M % 3 == 0;
@@ -224,7 +249,7 @@ struct Plan {
     static constexpr int radix(int P)
     {
         return !R3 ? (M / P >= 8 ? 8 : M / P)
-                   : (M / P == 3 ? 3 : (M / P % 12 == 0 ? 4 : 2));
+                   : (M / P == 12 ? 12 : (M / P == 24 ? 2 : 4));
     }
 };
 
