@@ -165,7 +165,7 @@ hipError_t launch_zmul(int prec, const Geom &g, void *S, const void *Nt, const v
 int zmul_auto_tile(int prec, const Geom &g);
 hipError_t launch_update(int prec, int mode, const Geom &g, const UpdArgs &a,
                          const void *tw, hipStream_t s, int *nblocks_out);
-int update_rows_per_block(int prec, const Geom &g);
+int update_rows_per_block(int prec, const Geom &g, bool step);
 // Raise the LDS limits of the update kernels and of the x pass above 64 KiB
 // where their smallest tiles need it (FP64 at 1024 points); once per device
 hipError_t prepare_update(int prec, const Geom &g);

@@ -106,7 +106,8 @@ struct tdgl_ctx {
     RkState *rk = nullptr;        // RK45 controller
     int *flag = nullptr;
     int cur = 0;
-    int yt = 2;
+    int yt = 2;                   // rows per group of the update kernel: steps, field
+    int yte = 2;                  // ... and energies (the order of their sums)
     // buffers only some models need: in a bound workspace after the core
     // regions (layout_of), otherwise allocated on first use (*_own)
     void *hist = nullptr;         // multistep: three E buffers
@@ -574,7 +575,7 @@ hipError_t enq_upd(tdgl_ctx *c, int mode, const void *Pin, const void *Pold, voi
     a.terms = terms;
     a.elec_in = elec_in ? 1 : 0;
     a.fx_out = fx_out ? 1 : 0;
-    a.yt = c->yt;
+    a.yt = mode == UPD_ENERGY ? c->yte : c->yt;
     return launch_update(c->prec, mode, c->g, a, tw(c), s, nullptr);
 }
 
@@ -744,7 +745,7 @@ hipError_t enq_relax_check(tdgl_ctx *c, const void *P, const RelaxArgs &ra, bool
     const bool el = elec_on(c);
     hipError_t e = enq_eval(c, UPD_ENERGY, P, nullptr, nullptr, 0, c->terms, el, false, s);
     if (e != hipSuccess) return e;
-    const int ngroups = ((c->g.ny + c->yt - 1) / c->yt) * c->g.nz;
+    const int ngroups = ((c->g.ny + c->yte - 1) / c->yte) * c->g.nz;
     e = launch_reduce_energies(c->partials, ngroups, c->g.nb, ra.joule, (double)ra.nmat, c->P0,
                                c->res, s);
     if (e != hipSuccess) return e;
@@ -893,7 +894,8 @@ tdgl_status tdgl_create_batch(const tdgl_grid *grid, int nbatch, int precision, 
     c->g.nt = nbatch == 1 ? 1 : 0;       // the built-in store mode (tdgl_set_store_mode)
     c->Tb.assign(nbatch, 300.0);
     c->layer.assign(n[2], 0);
-    c->yt = update_rows_per_block(c->prec, c->g);
+    c->yt = update_rows_per_block(c->prec, c->g, true);
+    c->yte = update_rows_per_block(c->prec, c->g, false);
     c->nblocks = ((c->g.ny + 1) / 2) * c->g.nz;   // partial sums for any row tile >= 2
     *out = c;
     return TDGL_OK;
@@ -1168,12 +1170,15 @@ tdgl_status tdgl_set_update_rows(tdgl_ctx *c, int rows)
     if (!c) return TDGL_E_ARG;
     if (rows < 0 || rows > 64 || rows == 1 || (rows & (rows - 1)))
         return fail(c, TDGL_E_ARG, "rows must be 0 or a power of two in 2..64");
-    const int yt = rows == 0 ? update_rows_per_block(c->prec, c->g) : rows;
+    const int yt = rows == 0 ? update_rows_per_block(c->prec, c->g, true) : rows;
+    const int yte = rows == 0 ? update_rows_per_block(c->prec, c->g, false) : rows;
     // the launch checks threads and LDS; probe with a zero-size query here
-    const int nb = ((c->g.ny + yt - 1) / yt) * c->g.nz;
+    const int ylow = std::min(yt, yte);
+    const int nb = ((c->g.ny + ylow - 1) / ylow) * c->g.nz;
     if (c->dev_init && nb > c->nblocks)
         return fail(c, TDGL_E_STATE, "more row groups than the workspace was sized for");
     c->yt = yt;
+    c->yte = yte;
     if (!c->dev_init) c->nblocks = nb > c->nblocks ? nb : c->nblocks;
     drop_graphs(c);
     return TDGL_OK;
@@ -1507,7 +1512,7 @@ tdgl_status energies_all(tdgl_ctx *c, double *F, double *meanP)
                         c->stream));
     if (el) c->spec_valid = false;
     // one partial per work-group of the launch just made, instance-major
-    const int ngroups = ((c->g.ny + c->yt - 1) / c->yt) * c->g.nz;
+    const int ngroups = ((c->g.ny + c->yte - 1) / c->yte) * c->g.nz;
     HIP_TRY(c, launch_reduce_partials(c->partials, ngroups, c->g.nb, c->res, c->stream));
     std::vector<double> r((size_t)8 * c->g.nb);
     HIP_TRY(c, hipMemcpyAsync(r.data(), c->res, r.size() * sizeof(double), hipMemcpyDeviceToHost,
@@ -1563,7 +1568,7 @@ tdgl_status tdgl_energies_noalloc(tdgl_ctx *c, double *out_dev)
         tdgl_status st = check_model(c);
         if (st != TDGL_OK) return st;
     }
-    const int ngroups = ((c->g.ny + c->yt - 1) / c->yt) * c->g.nz;
+    const int ngroups = ((c->g.ny + c->yte - 1) / c->yte) * c->g.nz;
     const size_t need = (size_t)ngroups * c->g.nb * 8;
     if (need > SCRATCH_DOUBLES)
         return fail(c, TDGL_E_UNSUPPORTED,
@@ -2120,7 +2125,7 @@ tdgl_status tdgl_autotune(tdgl_ctx *c, int nsteps, int choice[2], double *ms_per
     }
     // the winner stays set; the state goes back to what it was
     c->fft_path = best_path;
-    c->yt = best_yt;
+    c->yt = c->yte = best_yt;
     c->ztile = best_zt;
     c->g.nt = best_nt;
     c->graph_chunk = chunk0;

@@ -621,19 +621,39 @@ static int update_threads(const Geom &g, int yt, int tpl)
 
 // Rows per work-group: a power of two, limited by threads (<= 2 cells per
 // thread, <= 1024 FP32 / 512 FP64 threads) and 64 KiB of LDS.
+//
+// For the sums of an energy (step = false) the rows set the order of the partial
+// sums, so they depend on the instance's grid alone: at most 8 rows for FP32
+// and 4 for FP64, 2 for rows of 512 points or more.
+//
+// For time steps, where results do not depend on the rows, the most that leave
+// 256 groups (one per CU), 400 for FP64, over all instances: the fixed phases of
+// a group are then paid less often, while fewer groups leave CUs idle.  Heun steps in us at
+// 4 / 8 / 16 rows: 24 boxes of 32x32x32 FP32 188 / 158 / 148, FP64 335 / 267 / 238;
+// 128x128x32 film FP32 61.7 / 60.5 / 59.5, FP64 98.3 / 93.4 / -; one 64x64x16 box
+// FP32 41.5 / 43.8 / 45.2 (256 groups at 4); 4 films of 128x64x10 FP64 86 / 89 / - (320
+// groups at 8).  Long rows fill a group with few of
+// them: at most 4 FP32 rows of 192 or 256 points (16 boxes of 96x96x8 206 / 217 /
+// 210), 8 of 384 (190x180x20 216 / 207 / -), 8 FP64 rows from 96 points on (8 boxes
+// of 48x40x12 120 / 109 / 122), 2 from 512.  Small grids keep 8 short or 4 longer
+// rows.
 template <typename T, int M>
-static int rows_for(const Geom &g)
+static int rows_for(const Geom &g, bool step)
 {
     const int maxthr = UpdMaxThreads<T>::v;
     const int ny_even = g.ny + (g.ny & 1);
     int best = 2;
-    // at most 8 rows for FP32 and 4 for FP64, 2 for rows of 512 points or
-    // more (measured best on the 128x128x32 film and the 256x256x64
-    // bilayer; tdgl_autotune picks per grid)
-    const int ymax = M >= 512 ? 2 : (sizeof(T) == 4 ? 8 : 4);
+    const int ymax = M >= 512 ? 2
+                     : !step  ? (sizeof(T) == 4 ? 8 : 4)
+                              : (sizeof(T) == 4 ? (M > 256 ? 8 : (M >= 192 ? 4 : 16))
+                                              : (M >= 96 ? 8 : 16));
+    const int ymin = M <= 48 ? 8 : 4;
     for (int yt = 2; yt <= ymax && yt <= (ny_even > 2 ? ny_even : 2); yt *= 2) {
         if (update_threads(g, yt, HalfLine<M / 2>::TPL) > maxthr) break;
         if (yt > 2 && update_lds<T, M>(g, yt) > 65536) break;
+        if (step && yt > ymin &&
+            (long long)((g.ny + yt - 1) / yt) * g.nz * g.nb < (sizeof(T) == 4 ? 256 : 400))
+            break;
         best = yt;
     }
     return best;
@@ -641,24 +661,24 @@ static int rows_for(const Geom &g)
 
 #define TDGL_ROWS_LEN(T)                                   \
     switch (g.mx) {                                        \
-    case 8: return rows_for<T, 8>(g);                      \
-    case 16: return rows_for<T, 16>(g);                    \
-    case 24: return rows_for<T, 24>(g);                    \
-    case 32: return rows_for<T, 32>(g);                    \
-    case 48: return rows_for<T, 48>(g);                    \
-    case 64: return rows_for<T, 64>(g);                    \
-    case 96: return rows_for<T, 96>(g);                    \
-    case 128: return rows_for<T, 128>(g);                  \
-    case 192: return rows_for<T, 192>(g);                  \
-    case 256: return rows_for<T, 256>(g);                  \
-    case 384: return rows_for<T, 384>(g);                  \
-    case 512: return rows_for<T, 512>(g);                  \
-    case 768: return rows_for<T, 768>(g);                  \
-    case 1024: return rows_for<T, 1024>(g);                \
+    case 8: return rows_for<T, 8>(g, step);                \
+    case 16: return rows_for<T, 16>(g, step);              \
+    case 24: return rows_for<T, 24>(g, step);              \
+    case 32: return rows_for<T, 32>(g, step);              \
+    case 48: return rows_for<T, 48>(g, step);              \
+    case 64: return rows_for<T, 64>(g, step);              \
+    case 96: return rows_for<T, 96>(g, step);              \
+    case 128: return rows_for<T, 128>(g, step);            \
+    case 192: return rows_for<T, 192>(g, step);            \
+    case 256: return rows_for<T, 256>(g, step);            \
+    case 384: return rows_for<T, 384>(g, step);            \
+    case 512: return rows_for<T, 512>(g, step);            \
+    case 768: return rows_for<T, 768>(g, step);            \
+    case 1024: return rows_for<T, 1024>(g, step);          \
     default: return 2;                                     \
     }
 
-int update_rows_per_block(int prec, const Geom &g)
+int update_rows_per_block(int prec, const Geom &g, bool step)
 {
     if (prec == PREC_F32) {
         TDGL_ROWS_LEN(float)
