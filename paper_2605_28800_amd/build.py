@@ -14,7 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libtdgl.so")
 OBJDIR = os.path.join(ROOT, "_build")
-SOURCES = ["fft_passes.hip", "update.hip", "tensor.hip", "net.hip", "tdgl_api.cpp",
+SOURCES = ["slab.hip", "fft_passes.hip", "update.hip", "tensor.hip", "net.hip", "tdgl_api.cpp",
            "net_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

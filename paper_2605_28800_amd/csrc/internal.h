@@ -84,7 +84,8 @@ struct Freeze {
 // stores E; 3: Adams-Moulton corrector).
 // UPD_STEP_RK: stage s = 1..7 of the RK45 step (stages 1-6 store k_s and
 // form the next stage point; stage 7 stores k_7 and reduces the error).
-enum { UPD_STEP = 0, UPD_FIELD = 1, UPD_ENERGY = 2, UPD_STEP_MS = 3, UPD_STEP_RK = 4 };
+// UPD_FX (k_slab only): the spectra of P_in.
+enum { UPD_STEP = 0, UPD_FIELD = 1, UPD_ENERGY = 2, UPD_STEP_MS = 3, UPD_STEP_RK = 4, UPD_FX = 5 };
 
 struct UpdArgs {
     const void *P_in;      // state the field is evaluated at
@@ -123,9 +124,12 @@ struct RkState {
     int row;                             // rejections in a row
     int fail;                            // 1: error estimate not finite, 2: 64 in a row
     int keep;                            // k_rk_copy: the attempt was not accepted
-    int spectra;                         // k_fx: the spectra need no remaking
-    int stop[1];                         // frozen flags, one per instance
 };
+// behind it, one flag per instance each: frozen, and "the spectra need no
+// remaking" (the x pass after a rejection)
+constexpr size_t rk_bytes(int nb) { return sizeof(RkState) + 2 * sizeof(int) * (size_t)nb; }
+__host__ __device__ inline int *rk_stop(RkState *r) { return reinterpret_cast<int *>(r + 1); }
+__host__ __device__ inline int *rk_have(RkState *r, int nb) { return rk_stop(r) + nb; }
 hipError_t launch_rk_begin(RkState *r, int nb, double h, double atol, double rtol,
                            long long target, hipStream_t s);
 hipError_t launch_rk_control(RkState *r, int nb, const double *partials, int n, hipStream_t s);
@@ -166,6 +170,15 @@ int zmul_auto_tile(int prec, const Geom &g);
 hipError_t launch_update(int prec, int mode, const Geom &g, const UpdArgs &a,
                          const void *tw, hipStream_t s, int *nblocks_out);
 int update_rows_per_block(int prec, const Geom &g, bool step);
+// the two-kernel evaluation (slab.hip): spectra of slab_elements complex
+// values; UpdArgs as for launch_update with S1 the slab spectra
+bool slab_fits(const Geom &g);
+size_t slab_elements(const Geom &g);
+hipError_t prepare_slab(int prec, const Geom &g);
+hipError_t launch_slab(int prec, int mode, const Geom &g, const UpdArgs &a, const void *tw,
+                       hipStream_t s);
+hipError_t launch_ymul(int prec, const Geom &g, void *S, const void *Nt, const void *tw,
+                       hipStream_t s);
 // Raise the LDS limits of the update kernels and of the x pass above 64 KiB
 // where their smallest tiles need it (FP64 at 1024 points); once per device
 hipError_t prepare_update(int prec, const Geom &g);

@@ -121,7 +121,8 @@ struct tdgl_ctx {
     size_t lds_max = 65536;      // dynamic LDS one work-group may use on this device
     int fft_path = 0;            // 0: fused plane pass when it fits, 1: three passes
     int ztile = 0;               // z-pass column tile, bytes per z row (0: built-in choice)
-    bool use_plane = false;
+    bool use_plane = false;      // the fused plane pass
+    bool use_slab = false;       // the two-kernel evaluation (slab.hip), spectra in S2
     int nblocks = 1;
     bool P_set = false, tensor_built = false, spec_valid = false, params_dirty = true;
     int mimg = -1;
@@ -174,7 +175,8 @@ Layout layout_of(const tdgl_ctx *c, int scheme)
     };
     L.P = take(2 * 3 * N * c->esz);
     L.S1 = take((size_t)3 * g.nb * g.nz * g.ny * hx_blocked(g.hx) * 2 * c->esz);
-    L.S2 = take((size_t)3 * g.nb * g.nz * g.my * hx_blocked(g.hx) * 2 * c->esz);
+    const size_t s2 = (size_t)3 * g.nb * g.nz * g.my * hx_blocked(g.hx);
+    L.S2 = take((slab_fits(g) ? std::max(s2, slab_elements(g)) : s2) * 2 * c->esz);
     L.Nt = take((size_t)6 * (g.mz / 2 + 1) * (g.my / 2 + 1) * hx_blocked(g.hx) * c->esz);
     L.coef = take((size_t)g.nb * g.nz * NCOEF * c->esz);
     L.kp = take(sizeof(KParams<double>));
@@ -185,7 +187,7 @@ Layout layout_of(const tdgl_ctx *c, int scheme)
     L.flag = take(sizeof(int));
     L.res = take((size_t)8 * g.nb * sizeof(double));
     L.rlx = take(RLX_BYTES_PER_INSTANCE * g.nb + 32);
-    L.rk = take(sizeof(RkState) + sizeof(int) * g.nb);
+    L.rk = take(rk_bytes(g.nb));
     const size_t pbytes = 3 * N * c->esz;
     L.xbuf = take(pbytes);
     L.extra = off;
@@ -381,10 +383,13 @@ constexpr int PLANE_POINTS = 512;
 
 void choose_path(tdgl_ctx *c)
 {
-    c->use_plane = c->fft_path == 0 && c->g.nz * c->g.my <= PLANE_POINTS &&
+    c->use_slab = c->fft_path == 0 && slab_fits(c->g) && prepare_slab(c->prec, c->g) == hipSuccess;
+    c->use_plane = !c->use_slab && c->fft_path == 0 && c->g.nz * c->g.my <= PLANE_POINTS &&
                    launch_plane(c->prec, c->g, nullptr, nullptr, nullptr, c->lds_max, nullptr,
                                 true) == hipSuccess;
 }
+
+bool fused(const tdgl_ctx *c) { return c->use_plane || c->use_slab; }
 
 // ---- reduced parameters (Table 2 with alpha_ref in place of |alpha1|)
 void landau_si(const tdgl_material &m, double T, double out[8])
@@ -508,9 +513,17 @@ void drop_graphs(tdgl_ctx *c)
 bool elec_on(const tdgl_ctx *c) { return (c->terms & TDGL_ELEC) != 0; }
 
 // ---- enqueue helpers
+// the spectra of P that a field evaluation starts from
 hipError_t enq_fx(tdgl_ctx *c, const void *P, hipStream_t s)
 {
     const Geom &g = c->g;
+    if (c->use_slab) {
+        UpdArgs a{};
+        a.P_in = P;
+        a.S1 = c->S2;
+        a.kp = c->kp;
+        return launch_slab(c->prec, UPD_FX, g, a, tw(c), s);
+    }
     const long long rows = 3LL * g.nb * g.nz * g.ny;      // rows of all instances
     const Freeze fz{g.frozen, 3LL * g.nz * g.ny, g.nb};   // rows [nb][3][nz][ny]
     return launch_fx(c->prec, g.mx, P, rows, g.nx, g.nx, c->S1, rows, tw(c), s, fz, true);
@@ -539,6 +552,7 @@ hipError_t enq_yinv(tdgl_ctx *c, hipStream_t s, bool freeze = true)
 hipError_t enq_yz(tdgl_ctx *c, hipStream_t s)
 {
     const Geom &g = c->g;
+    if (c->use_slab) return launch_ymul(c->prec, g, c->S2, c->Nt, tw(c), s);
     if (c->use_plane) return launch_plane(c->prec, g, c->S1, c->Nt, tw(c), c->lds_max, s, false);
     hipError_t e = enq_yfwd(c, s);
     if (e != hipSuccess) return e;
@@ -554,6 +568,20 @@ hipError_t enq_cross(tdgl_ctx *c, const void *Pin, unsigned terms, UpdArgs &a, h
     if (!(terms & TDGL_GRAD) || !cross_terms(c) || !c->xbuf) return hipSuccess;
     a.cross = c->xbuf;
     return launch_cross(c->prec, c->g, Pin, c->xbuf, c->coef, c->kp, s);
+}
+
+// the update kernel of the evaluation's path
+hipError_t enq_kernel(tdgl_ctx *c, int mode, UpdArgs a, hipStream_t s)
+{
+    if (!c->use_slab || !a.elec_in) return launch_update(c->prec, mode, c->g, a, tw(c), s, nullptr);
+    a.S1 = c->S2;
+    return launch_slab(c->prec, mode, c->g, a, tw(c), s);
+}
+
+// work-groups per instance of a launch of it: one partial result each
+int partial_groups(const tdgl_ctx *c, bool elec, int yt)
+{
+    return c->use_slab && elec ? c->g.ny : ((c->g.ny + yt - 1) / yt) * c->g.nz;
 }
 
 hipError_t enq_upd(tdgl_ctx *c, int mode, const void *Pin, const void *Pold, void *Pout,
@@ -576,7 +604,7 @@ hipError_t enq_upd(tdgl_ctx *c, int mode, const void *Pin, const void *Pold, voi
     a.elec_in = elec_in ? 1 : 0;
     a.fx_out = fx_out ? 1 : 0;
     a.yt = mode == UPD_ENERGY ? c->yte : c->yt;
-    return launch_update(c->prec, mode, c->g, a, tw(c), s, nullptr);
+    return enq_kernel(c, mode, a, s);
 }
 
 hipError_t enq_eval(tdgl_ctx *c, int mode, const void *Pin, const void *Pold, void *Pout,
@@ -622,7 +650,7 @@ hipError_t enq_step_ms(tdgl_ctx *c, int cur, int *count, int *pos, hipStream_t s
     if (*count < 2) {                                   // start-up: Heun, storing E_n
         a.stage = 0;
         e = enq_cross(c, A, t, a, s);
-        if (e == hipSuccess) e = launch_update(c->prec, UPD_STEP_MS, c->g, a, tw(c), s, nullptr);
+        if (e == hipSuccess) e = enq_kernel(c, UPD_STEP_MS, a, s);
         if (e != hipSuccess) return e;
         e = enq_eval(c, UPD_STEP, B, A, A, 1, t, el, el, s);
     } else {
@@ -630,7 +658,7 @@ hipError_t enq_step_ms(tdgl_ctx *c, int cur, int *count, int *pos, hipStream_t s
         a.hist_a = hist_buf(c, *pos);
         a.hist_b = hist_buf(c, (*pos + 2) % 3);
         e = enq_cross(c, A, t, a, s);
-        if (e == hipSuccess) e = launch_update(c->prec, UPD_STEP_MS, c->g, a, tw(c), s, nullptr);
+        if (e == hipSuccess) e = enq_kernel(c, UPD_STEP_MS, a, s);
         if (e != hipSuccess) return e;
         if (el) e = enq_yz(c, s);                       // AM2 corrector -> A
         if (e != hipSuccess) return e;
@@ -642,7 +670,7 @@ hipError_t enq_step_ms(tdgl_ctx *c, int cur, int *count, int *pos, hipStream_t s
         a.hist_a = hist_buf(c, nw);
         a.hist_b = hist_buf(c, *pos);
         e = enq_cross(c, B, t, a, s);
-        if (e == hipSuccess) e = launch_update(c->prec, UPD_STEP_MS, c->g, a, tw(c), s, nullptr);
+        if (e == hipSuccess) e = enq_kernel(c, UPD_STEP_MS, a, s);
     }
     if (e != hipSuccess) return e;
     *pos = nw;
@@ -745,7 +773,7 @@ hipError_t enq_relax_check(tdgl_ctx *c, const void *P, const RelaxArgs &ra, bool
     const bool el = elec_on(c);
     hipError_t e = enq_eval(c, UPD_ENERGY, P, nullptr, nullptr, 0, c->terms, el, false, s);
     if (e != hipSuccess) return e;
-    const int ngroups = ((c->g.ny + c->yte - 1) / c->yte) * c->g.nz;
+    const int ngroups = partial_groups(c, el, c->yte);
     e = launch_reduce_energies(c->partials, ngroups, c->g.nb, ra.joule, (double)ra.nmat, c->P0,
                                c->res, s);
     if (e != hipSuccess) return e;
@@ -1160,6 +1188,7 @@ tdgl_status tdgl_set_fft_path(tdgl_ctx *c, int path)
     if (!c) return TDGL_E_ARG;
     if (path != 0 && path != 1) return fail(c, TDGL_E_ARG, "path must be 0 or 1");
     c->fft_path = path;
+    c->spec_valid = false;        // the paths keep their spectra in different orders
     drop_graphs(c);
     if (c->dev_init) choose_path(c);
     return TDGL_OK;
@@ -1220,7 +1249,7 @@ tdgl_status tdgl_get_z_tile(const tdgl_ctx *c, int *row_bytes)
 tdgl_status tdgl_get_fft_path(const tdgl_ctx *c, int *fused)
 {
     if (!c || !fused) return TDGL_E_ARG;
-    *fused = c->use_plane ? 1 : 0;
+    *fused = c->use_plane || c->use_slab ? 1 : 0;
     return TDGL_OK;
 }
 
@@ -1330,7 +1359,7 @@ hipError_t enq_rk_attempt(tdgl_ctx *c, hipStream_t s)
     a.rk_base = Pn;
     a.rk_k = static_cast<char *>(c->rkbuf) + pbytes;
     a.rk = c->rk;
-    c->g.frozen = c->rk->stop;
+    c->g.frozen = rk_stop(c->rk);
     hipError_t e = hipSuccess;
     // stage st reads the point written by stage st - 1; the fifth-order
     // solution (stage 6 output) lands in W0
@@ -1342,18 +1371,17 @@ hipError_t enq_rk_attempt(tdgl_ctx *c, hipStream_t s)
         a.P_in = in;
         a.P_out = out;
         if (e == hipSuccess) e = enq_cross(c, in, c->terms, a, s);
-        if (e == hipSuccess) e = launch_update(c->prec, UPD_STEP_RK, c->g, a, tw(c), s, nullptr);
+        if (e == hipSuccess) e = enq_kernel(c, UPD_STEP_RK, a, s);
         in = out;
     }
     c->g.frozen = nullptr;
-    const int ngroups = ((c->g.ny + c->yt - 1) / c->yt) * c->g.nz * c->g.nb;
+    const int ngroups = partial_groups(c, el, c->yt) * c->g.nb;
     if (e == hipSuccess) e = launch_rk_control(c->rk, c->g.nb, c->partials, ngroups, s);
     if (e == hipSuccess) e = launch_rk_copy(c->rk, W0, Pn, pbytes, s);
-    if (e == hipSuccess && el) {          // after a rejection: the x spectra of P_n again
-        const Geom &g = c->g;
-        const long long rows = 3LL * g.nb * g.nz * g.ny;
-        e = launch_fx(c->prec, g.mx, Pn, rows, g.nx, g.nx, c->S1, rows, tw(c), s,
-                      Freeze{&c->rk->spectra, rows, 1}, true);
+    if (e == hipSuccess && el) {          // after a rejection: the spectra of P_n again
+        c->g.frozen = rk_have(c->rk, c->g.nb);
+        e = enq_fx(c, Pn, s);
+        c->g.frozen = nullptr;
     }
     return e;
 }
@@ -1512,7 +1540,7 @@ tdgl_status energies_all(tdgl_ctx *c, double *F, double *meanP)
                         c->stream));
     if (el) c->spec_valid = false;
     // one partial per work-group of the launch just made, instance-major
-    const int ngroups = ((c->g.ny + c->yte - 1) / c->yte) * c->g.nz;
+    const int ngroups = partial_groups(c, el, c->yte);
     HIP_TRY(c, launch_reduce_partials(c->partials, ngroups, c->g.nb, c->res, c->stream));
     std::vector<double> r((size_t)8 * c->g.nb);
     HIP_TRY(c, hipMemcpyAsync(r.data(), c->res, r.size() * sizeof(double), hipMemcpyDeviceToHost,
@@ -1568,14 +1596,17 @@ tdgl_status tdgl_energies_noalloc(tdgl_ctx *c, double *out_dev)
         tdgl_status st = check_model(c);
         if (st != TDGL_OK) return st;
     }
-    const int ngroups = ((c->g.ny + c->yte - 1) / c->yte) * c->g.nz;
-    const size_t need = (size_t)ngroups * c->g.nb * 8;
+    const size_t need = (size_t)((c->g.ny + c->yte - 1) / c->yte) * c->g.nz * c->g.nb * 8;
     if (need > SCRATCH_DOUBLES)
         return fail(c, TDGL_E_UNSUPPORTED,
                     "energy partials need %zu doubles; the fixed scratch holds %zu "
                     "(use tdgl_energies_batch)", need, (size_t)SCRATCH_DOUBLES);
     double *scr = nullptr;
     HIP_TRY(c, scratch_address(&scr));
+    // (the two-kernel evaluation may have more groups than the rows it is
+    // admitted by: then the context's own partials, which hold them)
+    const int ngroups = partial_groups(c, el, c->yte);
+    if ((size_t)ngroups * c->g.nb * 8 > SCRATCH_DOUBLES) scr = c->partials;
     tdgl_status st = upload_params(c);      // no allocation: the workspace holds every buffer
     if (st != TDGL_OK) return st;
     if (el && !c->spec_valid) HIP_TRY(c, enq_fx(c, c->P[c->cur], c->stream));
@@ -1865,8 +1896,8 @@ tdgl_status tdgl_profile_step(tdgl_ctx *c, int nsteps, double ms_out[5])
             hipEvent_t *E = &ev[k];
             k += 5;
             (void)hipEventRecord(E[0], c->stream);
-            if (el && c->use_plane) {
-                le = launch_plane(c->prec, g, c->S1, c->Nt, tw(c), c->lds_max, c->stream, false);
+            if (el && fused(c)) {
+                le = enq_yz(c, c->stream);
                 (void)hipEventRecord(E[1], c->stream);
                 (void)hipEventRecord(E[2], c->stream);
                 (void)hipEventRecord(E[3], c->stream);
@@ -1897,7 +1928,7 @@ tdgl_status tdgl_profile_step(tdgl_ctx *c, int nsteps, double ms_out[5])
             k += 5;
             float ms;
             if (el) {
-                for (int q = 0; q < (c->use_plane ? 1 : 3); ++q) {
+                for (int q = 0; q < (fused(c) ? 1 : 3); ++q) {
                     (void)hipEventElapsedTime(&ms, E[q], E[q + 1]);
                     sum[q] += ms;
                     cnt[q]++;
@@ -1945,8 +1976,7 @@ tdgl_status tdgl_profile_kernels(tdgl_ctx *c, int nrep, double ms_out[5])
         auto launch = [&](hipStream_t s) -> hipError_t {
             switch (which) {
             case 0:
-                if (c->use_plane)
-                    return launch_plane(c->prec, g, c->S1, c->Nt, tw(c), c->lds_max, s, false);
+                if (fused(c)) return enq_yz(c, s);
                 return enq_yfwd(c, s, false);
             case 1: return launch_zmul(c->prec, g, c->S2, c->Nt, tw(c), c->ztile, s);
             case 2: return enq_yinv(c, s, false);
@@ -1981,8 +2011,8 @@ tdgl_status tdgl_profile_kernels(tdgl_ctx *c, int nrep, double ms_out[5])
     if (he == hipSuccess && c->scheme != TDGL_EULER) he = time_kernel(4, &ms_out[4]);
     if (el) {
         if (he == hipSuccess) he = time_kernel(0, &ms_out[0]);
-        if (he == hipSuccess && !c->use_plane) he = time_kernel(2, &ms_out[2]);
-        if (he == hipSuccess && !c->use_plane) he = time_kernel(1, &ms_out[1]);
+        if (he == hipSuccess && !fused(c)) he = time_kernel(2, &ms_out[2]);
+        if (he == hipSuccess && !fused(c)) he = time_kernel(1, &ms_out[1]);
     }
     // restore P and the flag whatever happened above
     hipError_t re = hipMemcpyAsync(c->P[c->cur], save, pbytes, hipMemcpyDeviceToDevice, c->stream);
@@ -2081,19 +2111,20 @@ tdgl_status tdgl_autotune(tdgl_ctx *c, int nsteps, int choice[2], double *ms_per
     for (int path = 0; path <= 1 && he == hipSuccess && rs == TDGL_OK; ++path) {
         c->fft_path = path;
         choose_path(c);
-        if (path == 0 && !c->use_plane) continue;   // the fused pass does not fit
+        if (path == 0 && !fused(c)) continue;       // no fused evaluation for this grid
         for (int yt = 2; yt <= 16 && he == hipSuccess && rs == TDGL_OK; yt *= 2) {
             if (((c->g.ny + yt - 1) / yt) * c->g.nz > nb_groups) continue;
             if (yt > 2 && yt > c->g.ny + (c->g.ny & 1)) break;
-            c->yt = yt;
+            c->yt = c->use_slab ? yt0 : yt;         // its groups are not row tiles
             c->ztile = 0;
             double ms = 0;
             if (trial(&ms) && ms < best) {
                 best = ms;
                 best_path = path;
-                best_yt = yt;
+                best_yt = c->yt;
                 best_zt = 0;
             }
+            if (c->use_slab) break;
         }
     }
     // then the z-pass tile of the three-pass path, with the rows found
@@ -2125,7 +2156,8 @@ tdgl_status tdgl_autotune(tdgl_ctx *c, int nsteps, int choice[2], double *ms_per
     }
     // the winner stays set; the state goes back to what it was
     c->fft_path = best_path;
-    c->yt = c->yte = best_yt;
+    c->yt = best_yt;
+    if (!(best_path == 0 && slab_fits(c->g))) c->yte = best_yt;
     c->ztile = best_zt;
     c->g.nt = best_nt;
     c->graph_chunk = chunk0;
@@ -2145,7 +2177,7 @@ tdgl_status tdgl_autotune(tdgl_ctx *c, int nsteps, int choice[2], double *ms_per
     if (he != hipSuccess) return fail(c, TDGL_E_HIP, "autotune: %s", hipGetErrorString(he));
     if (re != hipSuccess) return fail(c, TDGL_E_HIP, "state restore: %s", hipGetErrorString(re));
     if (best == 1e300) return fail(c, TDGL_E_HIP, "autotune: no candidate ran");
-    choice[0] = c->use_plane ? 1 : 0;
+    choice[0] = fused(c) ? 1 : 0;
     choice[1] = best_yt;
     if (ms_per_step) *ms_per_step = best;
     return TDGL_OK;

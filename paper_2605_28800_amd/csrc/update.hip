@@ -1000,7 +1000,10 @@ hipError_t launch_relax_test(const double *E, const RelaxState &r, int nb, bool 
 __global__ void k_rk_begin(RkState *r, int nb, double h, double atol, double rtol,
                            long long target)
 {
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) r->stop[b] = 0;
+    for (int b = threadIdx.x; b < nb; b += blockDim.x) {
+        rk_stop(r)[b] = 0;
+        rk_have(r, nb)[b] = 1;
+    }
     if (threadIdx.x == 0) {
         r->h = h;
         r->tau = 0.0;
@@ -1009,7 +1012,7 @@ __global__ void k_rk_begin(RkState *r, int nb, double h, double atol, double rto
         r->accepted = r->rejected = 0;
         r->target = target;
         r->row = r->fail = 0;
-        r->keep = r->spectra = 1;
+        r->keep = 1;
     }
 }
 
@@ -1018,14 +1021,18 @@ __global__ void k_rk_begin(RkState *r, int nb, double h, double atol, double rto
 __global__ void k_rk_control(RkState *r, int nb, const double *__restrict__ partials, int n)
 {
     __shared__ double red[256];
-    __shared__ int over;
+    __shared__ int over, have;
     const int tid = threadIdx.x;
     if (tid == 0) {
-        over = r->stop[0];
-        r->keep = r->spectra = 1;
+        over = rk_stop(r)[0];
+        have = 1;
+        r->keep = 1;
     }
     __syncthreads();
-    if (over) return;
+    if (over) {
+        for (int b = tid; b < nb; b += 256) rk_have(r, nb)[b] = 1;
+        return;
+    }
     double e = 0.0;
     for (int i = tid; i < n; i += 256) {
         const double v = partials[(long long)i * 8];
@@ -1051,14 +1058,16 @@ __global__ void k_rk_control(RkState *r, int nb, const double *__restrict__ part
         } else {
             r->h *= fac < 0.2 ? 0.2 : fac;
             ++r->rejected;
-            r->spectra = 0;
+            have = 0;
             if (++r->row == 64) r->fail = 2;
         }
         over = r->fail != 0 || r->accepted == r->target;
     }
     __syncthreads();
-    if (over)
-        for (int b = tid; b < nb; b += 256) r->stop[b] = 1;
+    for (int b = tid; b < nb; b += 256) {
+        rk_have(r, nb)[b] = have;
+        if (over) rk_stop(r)[b] = 1;
+    }
 }
 
 __global__ void k_rk_copy(const RkState *r, const uint2 *__restrict__ src, uint2 *__restrict__ dst,
