@@ -258,10 +258,11 @@ tdgl_status tdgl_get_fft_path(const tdgl_ctx *ctx, int *fused);
 tdgl_status tdgl_set_update_rows(tdgl_ctx *ctx, int rows);
 
 /* Column tile of the z pass: bytes of each z row a work-group loads (64,
- * 128 or 256; 0 restores the built-in choice: 128, or 64 where that leaves
- * fewer than 1024 work-groups).  A tuning knob: results do not depend on
- * it.  tdgl_get_z_tile reports the tile in use (the built-in choice
- * resolved). */
+ * 128 or 256; 0 restores the built-in choice: one wave per tile where there
+ * are enough of them, otherwise 128, or 64 where that leaves fewer than 1024
+ * work-groups).  A tuning knob: results do not depend on it.
+ * tdgl_get_z_tile reports the tile set, or the row tile of the built-in
+ * choice. */
 tdgl_status tdgl_set_z_tile(tdgl_ctx *ctx, int row_bytes);
 tdgl_status tdgl_get_z_tile(const tdgl_ctx *ctx, int *row_bytes);
 

@@ -92,13 +92,13 @@ __device__ __forceinline__ cpx<T> csub(cpx<T> a, cpx<T> b) { return {a.x - b.x, 
 template <typename T>
 __device__ __forceinline__ cpx<T> cmul(cpx<T> a, cpx<T> b)
 {
-    return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+    return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
 }
 // a * conj(b)
 template <typename T>
 __device__ __forceinline__ cpx<T> cmulc(cpx<T> a, cpx<T> b)
 {
-    return {a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y};
+    return {fma(a.x, b.x, a.y * b.y), fma(a.y, b.x, -(a.x * b.y))};
 }
 template <typename T>
 __device__ __forceinline__ cpx<T> cconj(cpx<T> a) { return {a.x, -a.y}; }
@@ -128,7 +128,10 @@ __device__ __forceinline__ void dft4(cpx<T> *v)
     v[3] = csub(t1, t3);
 }
 
-// 8-point DFT as radix-2 (n, n+4) pairs, W_8^n twiddles, two 4-point DFTs.
+// 8-point DFT as radix-2 (n, n+4) pairs, W_8^n twiddles, two 4-point DFTs.  The
+// factor 1/sqrt 2 of W_8 and W_8^3 enters by fused multiply-adds behind the sums
+// it is common to.  (The roundings are written out here and in cmul, so that
+// every kernel that uses a transform of one length gives the same bits.)
 template <typename T, bool INV>
 __device__ __forceinline__ void dft8(cpx<T> *v)
 {
@@ -139,22 +142,21 @@ __device__ __forceinline__ void dft8(cpx<T> *v)
         a[n] = cadd(v[n], v[n + 4]);
         b[n] = csub(v[n], v[n + 4]);
     }
-    {
-        cpx<T> u = b[1];
-        b[1] = INV ? cpx<T>{s * (u.x - u.y), s * (u.x + u.y)}
-                   : cpx<T>{s * (u.x + u.y), s * (u.y - u.x)};
-        b[2] = rot90<T, INV>(b[2]);
-        u = b[3];
-        b[3] = INV ? cpx<T>{-s * (u.x + u.y), s * (u.x - u.y)}
-                   : cpx<T>{s * (u.y - u.x), -s * (u.x + u.y)};
-    }
     dft4<T, INV>(a);
-    dft4<T, INV>(b);
+    const cpx<T> e = rot90<T, INV>(b[2]);
+    const cpx<T> t0 = cadd(b[0], e), t1 = csub(b[0], e);
+    // sqrt 2 W_8 b1 and sqrt 2 W_8^3 b3
+    const cpx<T> p = INV ? cpx<T>{b[1].x - b[1].y, b[1].x + b[1].y}
+                         : cpx<T>{b[1].x + b[1].y, b[1].y - b[1].x};
+    const cpx<T> q = INV ? cpx<T>{-(b[3].x + b[3].y), b[3].x - b[3].y}
+                         : cpx<T>{b[3].y - b[3].x, -(b[3].x + b[3].y)};
+    const cpx<T> t2 = cadd(p, q), t3 = rot90<T, INV>(csub(p, q));
+    v[1] = {fma(s, t2.x, t0.x), fma(s, t2.y, t0.y)};
+    v[5] = {fma(-s, t2.x, t0.x), fma(-s, t2.y, t0.y)};
+    v[3] = {fma(s, t3.x, t1.x), fma(s, t3.y, t1.y)};
+    v[7] = {fma(-s, t3.x, t1.x), fma(-s, t3.y, t1.y)};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        v[2 * k] = a[k];
-        v[2 * k + 1] = b[k];
-    }
+    for (int k = 0; k < 4; ++k) v[2 * k] = a[k];
 }
 
 // 3-point DFT: X0 = a + b + c, X1,2 = a - (b + c)/2 -/+ i (sqrt 3 / 2)(b - c)

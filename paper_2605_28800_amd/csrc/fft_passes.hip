@@ -271,6 +271,14 @@ __device__ __forceinline__ void tensor_row(const T *__restrict__ Nt, int kx, int
     n2 = b[r.i2 * qs] * odd_sign(r.i2, sy, sz);
 }
 
+// one component of the product, in a fixed order of roundings: both z passes
+// give the same bits
+template <typename T>
+__device__ __forceinline__ cpx<T> dot3(T n0, cpx<T> a, T n1, cpx<T> b, T n2, cpx<T> c)
+{
+    return {fma(n2, c.x, fma(n1, b.x, n0 * a.x)), fma(n2, c.y, fma(n1, b.y, n0 * a.y))};
+}
+
 // ------------------------------------------------- z pass with multiply
 // S: the KB-blocked y spectra (in place); work-group = (block of KB kx,
 // instance, tile of CT consecutive columns j = ky*KB + kx%KB) x 3
@@ -412,7 +420,7 @@ __global__ void __launch_bounds__((ZmulCfg<T, MZ, RB>::NTHR))
             const cpx<T> p1 = lds_get(&lds[1 * LZ * CT + o]);
             const cpx<T> p2 = lds_get(&lds[2 * LZ * CT + o]);
             const T n0 = nrow[q][0], n1 = nrow[q][1], n2 = nrow[q][2];
-            v[q] = {n0 * p0.x + n1 * p1.x + n2 * p2.x, n0 * p0.y + n1 * p1.y + n2 * p2.y};
+            v[q] = dot3(n0, p0, n1, p1, n2, p2);
         }
     }
     __syncthreads();
@@ -430,6 +438,128 @@ __global__ void __launch_bounds__((ZmulCfg<T, MZ, RB>::NTHR))
             const int z = t + q * TPL;
             const bool out = HALF ? q < 4 : z < nz;
             if (act && out) *at(plane, (col + (unsigned)z * myb) * CSZ) = v[q];
+        }
+    }
+}
+
+// ------------------------------------- z pass with multiply, a wave per tile
+// The same pass for launches of many tiles.  One wave has 64 / (mz/8) columns of
+// all three components: the multiply needs no exchange between threads (k_zmul
+// passes every spectrum value through LDS a second time and reads it back
+// three times), nothing waits for another wave, and each tensor value of the
+// tile is fetched once, 16 bytes a lane, straight to LDS, where kz and mz - kz
+// share it.  Those loads are the first to be issued, so they take no registers
+// and are there when the forward transforms end.  What bounds it: the vector
+// instructions of the transforms (about 13 us of the 15 to 21 below) next to
+// the spectra's traffic (16 us).  Bits are those of k_zmul.
+// z pass of 24 boxes of 32x32x32 FP32 30.8 -> 20.7 us, FP64 43.6 -> 35; 16 of
+// 96x96x8 FP32 29.7 -> 22.8; 24 of 64x64x16 FP32 39.5 -> 29.5; one of 64x64x64 FP32
+// 17.5 -> 13.6, FP64 41.7 -> 22.3; 100x100x50 FP32 70.8 -> 33.2.  Taken with the
+// tensor through registers instead: 25.6 us for the first.
+template <typename T, int MZ>
+struct ZcolCfg {
+    static constexpr int TPL = MZ / 8;             // threads of a column
+    static constexpr int CW = 64 / TPL;            // columns of a wave
+    static constexpr int SCR = LinePad<MZ>::len * CW * (int)sizeof(cpx<T>);   // scratch, bytes
+    // 16-byte items of the tensor, 64 a load
+    static constexpr int NTEN = (6 * (MZ / 2 + 1) * CW * (int)sizeof(T) / 16 + 63) / 64;
+};
+
+template <typename T, int MZ, bool HALF>
+__global__ void __launch_bounds__(64)
+    k_zcol(cpx<T> *S, const T *__restrict__ Nt, int nz, int my, int hx, int nb,
+           const cpx<T> *__restrict__ tw, const int *__restrict__ frozen, unsigned gx,
+           unsigned mgx, unsigned mnb, int nt)
+{
+    using C = ZcolCfg<T, MZ>;
+    constexpr int TPL = C::TPL, CW = C::CW, NKY = CW / KB;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int lane = threadIdx.x, cc = lane & (CW - 1), t = lane / CW;
+    cpx<T> *L = reinterpret_cast<cpx<T> *>(smem_raw) + cc;
+    const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+    const unsigned kbb = udiv(tile, gx, mgx);                  // (kx block, instance)
+    const unsigned kblk = udiv(kbb, (unsigned)nb, mnb);
+    if (frozen && frozen[kbb - kblk * nb]) return;
+    const int myb = my * KB;                         // columns of a block plane
+    const int ky0 = (int)(tile - kbb * gx) * NKY, j = ky0 * KB + cc;
+    const int ky = j >> KBS;
+    const bool act = j < myb && (int)kblk * KB + (j & (KB - 1)) < hx;
+    cpx<T> *plane = S + (long long)kbb * 3 * nz * myb;
+    const unsigned col = act ? j : 0;
+    constexpr unsigned CSZ = sizeof(cpx<T>), SZ = sizeof(T);
+    // the octant's values of the wave's columns, once each, straight to LDS: 16
+    // bytes per lane, item (comp, kz', ky, part of the KB kx)
+    const unsigned tlds =
+        (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)(smem_raw + C::SCR);
+    {
+        constexpr int HZ = MZ / 2 + 1, PARTS = KB * SZ / 16, NIT = 6 * HZ * NKY * PARTS;
+        const unsigned hy = my / 2 + 1;
+        const char *tb = reinterpret_cast<const char *>(Nt + (long long)kblk * 6 * HZ * hy * KB);
+#pragma unroll
+        for (int m = 0; m < C::NTEN; ++m) {
+            const int item = m * 64 + lane < NIT ? m * 64 + lane : 0;
+            const int part = item % PARTS, r = item / PARTS, ky = ky0 + r % NKY, kq = r / NKY;
+            const int kyo = ky > my / 2 ? (ky < my ? my - ky : 0) : ky;
+            const char *p = tb + ((unsigned)(kq * hy + kyo) * KB * SZ + part * 16);
+            const unsigned m0 = __builtin_amdgcn_readfirstlane((int)(tlds + m * 1024u));
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                         ::"s"(m0), "v"(p) : "memory", "m0");
+        }
+    }
+    cpx<T> v[3][8];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int z = t + q * TPL;
+            const bool in = HALF ? q < 4 : z < nz;
+            v[c][q] = (act && in) ? ld_at(plane, (col + (unsigned)(c * nz + z) * myb) * CSZ)
+                                  : cpx<T>{T(0), T(0)};
+        }
+    TwReg<T, MZ> tr;
+    twiddle_load(tr, tw, t);
+    const IdxStridePad ip{CW};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {                    // one scratch: a wave's LDS accesses keep
+        __builtin_amdgcn_sched_barrier(0);           // their order
+        fft_line<T, MZ, false, IdxStridePad, true>(v[c], L, ip, t, tr, true);
+        line_sync<true>();
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the tensor is in LDS
+    const T *nt_lds = reinterpret_cast<const T *>(smem_raw + C::SCR) + cc;
+    const T ys = ky > my / 2 ? T(-1) : T(1);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if (q % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+        const int kz = t + q * TPL;
+        const bool zneg = kz > MZ / 2;
+        const T *p = nt_lds + (zneg ? MZ - kz : kz) * CW;
+        constexpr int CS = (MZ / 2 + 1) * CW;
+        T m[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) m[i] = p[i * CS];
+        m[3] *= ys;
+        m[4] *= zneg ? T(-1) : T(1);
+        m[5] *= zneg ? -ys : ys;
+        const cpx<T> a = v[0][q], b = v[1][q], c = v[2][q];
+        v[0][q] = dot3(m[0], a, m[3], b, m[4], c);
+        v[1][q] = dot3(m[3], a, m[1], b, m[5], c);
+        v[2][q] = dot3(m[4], a, m[5], b, m[2], c);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        __builtin_amdgcn_sched_barrier(0);
+        fft_line<T, MZ, true, IdxStridePad, true>(v[c], L, ip, t, tr, true);
+        line_sync<true>();
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int z = t + q * TPL;
+            const bool out = HALF ? q < 4 : z < nz;
+            if (act && out) {
+                cpx<T> *p = at(plane, (col + (unsigned)(c * nz + z) * myb) * CSZ);
+                if (nt) st_nt(p, v[c][q]);
+                else *p = v[c][q];
+            }
         }
     }
 }
@@ -840,6 +970,25 @@ hipError_t launch_col(int prec, int M, bool inv, const void *in, void *out, long
     }
 }
 
+template <typename T, int MZ>
+static hipError_t zcol_impl(const Geom &g, void *S, const void *Nt, const void *tw, hipStream_t s)
+{
+    using C = ZcolCfg<T, MZ>;
+    const unsigned gx = (unsigned)(g.my * KB + C::CW - 1) / C::CW;
+    const int nkb = hx_blocked(g.hx) / KB;
+    if ((long long)nkb * g.nb > 65535) return hipErrorInvalidValue;
+    constexpr size_t shm = C::SCR + C::NTEN * 1024;
+    static_assert(shm <= 65536 && C::SCR % 16 == 0 && C::CW >= KB, "tile");
+    const unsigned long long ntile = (unsigned long long)gx * nkb * g.nb;
+    const unsigned mgx = div_magic(gx, ntile);
+    const unsigned mnb = div_magic((unsigned)g.nb, (unsigned long long)nkb * g.nb);
+    auto k = 2 * g.nz == MZ ? k_zcol<T, MZ, true> : k_zcol<T, MZ, false>;
+    hipLaunchKernelGGL(k, dim3((unsigned)ntile), dim3(64), shm, s, (cpx<T> *)S, (const T *)Nt,
+                       g.nz, g.my, g.hx, g.nb, (const cpx<T> *)tw + tw_off(MZ), g.frozen, gx, mgx,
+                       mnb, g.nt);
+    return hipGetLastError();
+}
+
 template <typename T, int MZ, int RB>
 static hipError_t zmul_tile(const Geom &g, void *S, const void *Nt, const void *tw, hipStream_t s)
 {
@@ -874,10 +1023,35 @@ int zmul_auto_tile(int prec, const Geom &g)
     return groups < 1024 ? 64 : 128;
 }
 
+// One wave per tile (k_zcol) where there are enough of them: a wave does three
+// times the work of one of k_zmul, one after the other.  us, k_zmul / k_zcol:
+//   FP32 mz <= 64: 64x64x16 4.7 / 5.7 (544 waves), 128x128x16 8.5 / 9.1 (2112), two
+//     14.4 / 14.5 (4224), 24x30x20 16 of them 18.0 / 13.3 (3584), 300x200x7 19.2 / 18.3
+//   FP64 mz <= 64, z half filled: 32x32x32 4 of them 10.5 / 10.4 (1152 waves), 12
+//     24.1 / 22.1 (3456), 128x128x16 16.2 / 15.9 (2112); otherwise the eight input rows
+//     of a component cost the second wave per SIMD: 60x60x10 4 of them 16.7 / 19.7
+//   mz = 128 (k_zmul: two groups of 12 waves per CU): FP32 8x8x40 6.7 / 6.5 (48 waves),
+//     32x32x64 9.0 / 7.7; FP64 8x8x40 6.4 / 7.4, 32x32x64 11.9 / 9.8 (576).  The FP32 tile
+//     is 32 bytes of each z row, which pays while the spectra stay in the 256 MB
+//     cache: 128x128x64 47 / 42 (105 MB), 200x200x64 171 / 245 (203 MB)
+template <typename T, int MZ>
+static bool zcol_wins(const Geom &g)
+{
+    const long long cols = (long long)hx_blocked(g.hx) * g.nb * g.my;
+    const long long waves = cols * (MZ / 8) / 64;
+    if (sizeof(T) == 8) return MZ == 128 ? waves >= 512 : 2 * g.nz == MZ && waves >= 2048;
+    if (MZ == 128) return 3 * cols * g.nz * (long long)sizeof(cpx<T>) <= 128LL << 20;
+    return waves >= 3200;
+}
+
 template <typename T, int MZ>
 static hipError_t zmul_impl(const Geom &g, void *S, const void *Nt, const void *tw, int rb,
                             hipStream_t s)
 {
+    if constexpr (MZ <= 128) {
+        if (rb == 0 && zcol_wins<T, MZ>(g)) return zcol_impl<T, MZ>(g, S, Nt, tw, s);
+    }
+    if (rb == 0) rb = zmul_auto_tile(sizeof(T) == 4 ? PREC_F32 : PREC_F64, g);
     switch (rb) {
     case 64: return zmul_tile<T, MZ, 64>(g, S, Nt, tw, s);
     case 128: return zmul_tile<T, MZ, 128>(g, S, Nt, tw, s);
@@ -889,7 +1063,7 @@ static hipError_t zmul_impl(const Geom &g, void *S, const void *Nt, const void *
 hipError_t launch_zmul(int prec, const Geom &g, void *S, const void *Nt, const void *tw,
                        int tile_bytes, hipStream_t s)
 {
-    const int rb = tile_bytes == 0 ? zmul_auto_tile(prec, g) : tile_bytes;
+    const int rb = tile_bytes;
     if (prec == PREC_F32) {
         TDGL_LEN_SWITCH(g.mz, return (zmul_impl<float, LEN_>(g, S, Nt, tw, rb, s)))
     } else {
