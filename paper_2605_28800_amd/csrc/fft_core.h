@@ -92,7 +92,7 @@ __device__ __forceinline__ cpx<T> csub(cpx<T> a, cpx<T> b) { return {a.x - b.x, 
 template <typename T>
 __device__ __forceinline__ cpx<T> cmul(cpx<T> a, cpx<T> b)
 {
-    return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
+    return {fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y)};
 }
 // a * conj(b)
 template <typename T>
@@ -128,10 +128,9 @@ __device__ __forceinline__ void dft4(cpx<T> *v)
     v[3] = csub(t1, t3);
 }
 
-// 8-point DFT as radix-2 (n, n+4) pairs, W_8^n twiddles, two 4-point DFTs.  The
-// factor 1/sqrt 2 of W_8 and W_8^3 enters by fused multiply-adds behind the sums
-// it is common to.  (The roundings are written out here and in cmul, so that
-// every kernel that uses a transform of one length gives the same bits.)
+// 8-point DFT as radix-2 (n, n+4) pairs, W_8^n twiddles, two 4-point DFTs.  (The
+// fused multiply-adds are written out here and in cmul, so that every kernel
+// that uses a transform of one length gives the same bits.)
 template <typename T, bool INV>
 __device__ __forceinline__ void dft8(cpx<T> *v)
 {
@@ -145,16 +144,16 @@ __device__ __forceinline__ void dft8(cpx<T> *v)
     dft4<T, INV>(a);
     const cpx<T> e = rot90<T, INV>(b[2]);
     const cpx<T> t0 = cadd(b[0], e), t1 = csub(b[0], e);
-    // sqrt 2 W_8 b1 and sqrt 2 W_8^3 b3
-    const cpx<T> p = INV ? cpx<T>{b[1].x - b[1].y, b[1].x + b[1].y}
-                         : cpx<T>{b[1].x + b[1].y, b[1].y - b[1].x};
-    const cpx<T> q = INV ? cpx<T>{-(b[3].x + b[3].y), b[3].x - b[3].y}
-                         : cpx<T>{b[3].y - b[3].x, -(b[3].x + b[3].y)};
-    const cpx<T> t2 = cadd(p, q), t3 = rot90<T, INV>(csub(p, q));
-    v[1] = {fma(s, t2.x, t0.x), fma(s, t2.y, t0.y)};
-    v[5] = {fma(-s, t2.x, t0.x), fma(-s, t2.y, t0.y)};
-    v[3] = {fma(s, t3.x, t1.x), fma(s, t3.y, t1.y)};
-    v[7] = {fma(-s, t3.x, t1.x), fma(-s, t3.y, t1.y)};
+    // t2, d = W_8 b1 +- W_8^3 b3: the sums' products rounded, the differences' fused
+    const T p = s * (b[1].x + b[1].y), q = -s * (b[3].x + b[3].y);
+    const T u = INV ? b[1].x - b[1].y : b[1].y - b[1].x, w = INV ? b[3].x - b[3].y : b[3].y - b[3].x;
+    const cpx<T> t2 = INV ? cpx<T>{fma(s, u, q), fma(s, w, p)} : cpx<T>{fma(s, w, p), fma(s, u, q)};
+    const cpx<T> d = INV ? cpx<T>{fma(s, u, -q), fma(-s, w, p)} : cpx<T>{fma(-s, w, p), fma(s, u, -q)};
+    const cpx<T> t3 = rot90<T, INV>(d);
+    v[1] = cadd(t0, t2);
+    v[5] = csub(t0, t2);
+    v[3] = cadd(t1, t3);
+    v[7] = csub(t1, t3);
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[2 * k] = a[k];
 }

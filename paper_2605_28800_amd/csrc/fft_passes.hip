@@ -276,7 +276,7 @@ __device__ __forceinline__ void tensor_row(const T *__restrict__ Nt, int kx, int
 template <typename T>
 __device__ __forceinline__ cpx<T> dot3(T n0, cpx<T> a, T n1, cpx<T> b, T n2, cpx<T> c)
 {
-    return {fma(n2, c.x, fma(n1, b.x, n0 * a.x)), fma(n2, c.y, fma(n1, b.y, n0 * a.y))};
+    return {fma(n2, c.x, fma(n0, a.x, n1 * b.x)), fma(n2, c.y, fma(n0, a.y, n1 * b.y))};
 }
 
 // ------------------------------------------------- z pass with multiply
