@@ -450,9 +450,9 @@ __global__ void __launch_bounds__((ZmulCfg<T, MZ, RB>::NTHR))
 // tile is fetched once, 16 bytes a lane, straight to LDS, where kz and mz - kz
 // share it.  Those loads are the first to be issued, so they take no registers
 // and are there when the forward transforms end.  What bounds it: the vector
-// instructions of the transforms (about 13 us of the 15 to 21 below) next to
+// instructions of the transforms (about 13 us of the first 20.7 below) next to
 // the spectra's traffic (16 us).  Bits are those of k_zmul.
-// z pass of 24 boxes of 32x32x32 FP32 30.8 -> 20.7 us, FP64 43.6 -> 35; 16 of
+// z pass of 24 boxes of 32x32x32 FP32 30.8 -> 20.7 us, FP64 43.6 -> 36; 16 of
 // 96x96x8 FP32 29.7 -> 22.8; 24 of 64x64x16 FP32 39.5 -> 29.5; one of 64x64x64 FP32
 // 17.5 -> 13.6, FP64 41.7 -> 22.3; 100x100x50 FP32 70.8 -> 33.2.  Taken with the
 // tensor through registers instead: 25.6 us for the first.
