@@ -170,10 +170,9 @@ int zmul_auto_tile(int prec, const Geom &g);
 hipError_t launch_update(int prec, int mode, const Geom &g, const UpdArgs &a,
                          const void *tw, hipStream_t s, int *nblocks_out);
 int update_rows_per_block(int prec, const Geom &g, bool step);
-// the two-kernel evaluation (slab.hip): spectra of slab_elements complex
-// values; UpdArgs as for launch_update with S1 the slab spectra
+// the two-kernel evaluation (slab.hip); UpdArgs as for launch_update, the slab
+// spectra from S1 on into S2 behind it
 bool slab_fits(const Geom &g);
-size_t slab_elements(const Geom &g);
 hipError_t prepare_slab(int prec, const Geom &g);
 hipError_t launch_slab(int prec, int mode, const Geom &g, const UpdArgs &a, const void *tw,
                        hipStream_t s);

@@ -15,6 +15,9 @@
 // kz, y) of instance b at ((((kx/8) nb + b) 3 + c) mz + kz) ny + y) 8 + kx%8 for
 // kx < mx/2, and the column kx = mx/2 behind them in tiles of 8 kz, at
 // (((b 3 + c) (mz/8) + kz/8) ny + y) 8 + kz%8: no tile is padded.
+// These 3 nb mz ny hx values fit into S1 and S2 together, 3 nb nz (ny + my) times
+// the hx of whole blocks: my >= 2 ny for a power of two, and slab_fits asks for
+// 3 nz >= mz.
 #include "cell.h"
 #include "fft_core.h"
 #include "internal.h"
@@ -28,8 +31,6 @@ __host__ __device__ __forceinline__ long long slab_main(const Geom &g)
 {
     return (long long)3 * g.nb * g.mz * g.ny * (g.mx / 2);
 }
-
-size_t slab_elements(const Geom &g) { return (size_t)3 * g.nb * g.mz * g.ny * g.hx; }
 
 // z transforms of the slab's 3 (M2 + 1) columns (c, kx): INV from S into the
 // rows U[(c nz + z)(M2 + 1) + kx], forward back.  Eight columns of a tile sit in

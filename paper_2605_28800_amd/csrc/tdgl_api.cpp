@@ -122,7 +122,7 @@ struct tdgl_ctx {
     int fft_path = 0;            // 0: fused plane pass when it fits, 1: three passes
     int ztile = 0;               // z-pass column tile, bytes per z row (0: built-in choice)
     bool use_plane = false;      // the fused plane pass
-    bool use_slab = false;       // the two-kernel evaluation (slab.hip), spectra in S2
+    bool use_slab = false;       // the two-kernel evaluation (slab.hip), spectra in S1 and S2
     int nblocks = 1;
     bool P_set = false, tensor_built = false, spec_valid = false, params_dirty = true;
     int mimg = -1;
@@ -175,8 +175,7 @@ Layout layout_of(const tdgl_ctx *c, int scheme)
     };
     L.P = take(2 * 3 * N * c->esz);
     L.S1 = take((size_t)3 * g.nb * g.nz * g.ny * hx_blocked(g.hx) * 2 * c->esz);
-    const size_t s2 = (size_t)3 * g.nb * g.nz * g.my * hx_blocked(g.hx);
-    L.S2 = take((slab_fits(g) ? std::max(s2, slab_elements(g)) : s2) * 2 * c->esz);
+    L.S2 = take((size_t)3 * g.nb * g.nz * g.my * hx_blocked(g.hx) * 2 * c->esz);   // behind S1
     L.Nt = take((size_t)6 * (g.mz / 2 + 1) * (g.my / 2 + 1) * hx_blocked(g.hx) * c->esz);
     L.coef = take((size_t)g.nb * g.nz * NCOEF * c->esz);
     L.kp = take(sizeof(KParams<double>));
@@ -520,7 +519,7 @@ hipError_t enq_fx(tdgl_ctx *c, const void *P, hipStream_t s)
     if (c->use_slab) {
         UpdArgs a{};
         a.P_in = P;
-        a.S1 = c->S2;
+        a.S1 = c->S1;
         a.kp = c->kp;
         return launch_slab(c->prec, UPD_FX, g, a, tw(c), s);
     }
@@ -552,7 +551,7 @@ hipError_t enq_yinv(tdgl_ctx *c, hipStream_t s, bool freeze = true)
 hipError_t enq_yz(tdgl_ctx *c, hipStream_t s)
 {
     const Geom &g = c->g;
-    if (c->use_slab) return launch_ymul(c->prec, g, c->S2, c->Nt, tw(c), s);
+    if (c->use_slab) return launch_ymul(c->prec, g, c->S1, c->Nt, tw(c), s);
     if (c->use_plane) return launch_plane(c->prec, g, c->S1, c->Nt, tw(c), c->lds_max, s, false);
     hipError_t e = enq_yfwd(c, s);
     if (e != hipSuccess) return e;
@@ -574,7 +573,6 @@ hipError_t enq_cross(tdgl_ctx *c, const void *Pin, unsigned terms, UpdArgs &a, h
 hipError_t enq_kernel(tdgl_ctx *c, int mode, UpdArgs a, hipStream_t s)
 {
     if (!c->use_slab || !a.elec_in) return launch_update(c->prec, mode, c->g, a, tw(c), s, nullptr);
-    a.S1 = c->S2;
     return launch_slab(c->prec, mode, c->g, a, tw(c), s);
 }
 
