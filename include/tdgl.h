@@ -217,8 +217,10 @@ tdgl_status tdgl_set_terms(tdgl_ctx *ctx, unsigned mask);
  * per attempt; dtau is the first trial step, tdgl_step(n) makes n accepted
  * steps (see tdgl_set_rk_tolerances); the step size and the decision on an
  * attempt stay on the device, and tdgl_step synchronises once per 64 steps and
- * once more for each group of rejections.  This call resets the RK45 time and
- * step. */
+ * once more for each group of rejections.  A call that meets an attempt whose
+ * error estimate is not finite (NaN included), or 64 rejections in a row, ends with
+ * TDGL_E_NONFINITE and leaves P at the last accepted step.  tdgl_set_integrator
+ * resets the RK45 time and step. */
 tdgl_status tdgl_set_integrator(tdgl_ctx *ctx, int scheme, double dtau);
 
 /* RK45 error control: an attempt is accepted when, over every cell and

@@ -27,6 +27,18 @@ __device__ __forceinline__ T landau_f(const T sq[3], const T *cf)
            cf[6] * (x * x * (y + z) + y * y * (x + z) + z * z * (x + y)) + cf[7] * x * y * z;
 }
 
+// One component's part of the RK45 error measure: |err| over the tolerance scale.
+// An error that is not a number counts as infinite, so that the maxima over
+// cells and groups, which drop NaN, keep it and the attempt fails; no error at
+// all counts as zero whatever the scale (vacuum cells with an absolute
+// tolerance of 0).
+template <typename T>
+__device__ __forceinline__ T rk_scaled(T err, T scale)
+{
+    const T r = fabs(err) / scale;
+    return err == T(0) ? T(0) : (r == r ? r : T(INFINITY));
+}
+
 // Dormand-Prince 5(4) tableau (Dormand & Prince 1980): row s of RK_A gives
 // the weights of k_1..k_s for the stage point s + 1 (row 6 is the
 // fifth-order solution); RK_E = fifth- minus fourth-order weights.

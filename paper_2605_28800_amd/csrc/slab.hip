@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(SLAB_THREADS)
                         T s = T(RK_E[6]) * e1;
                         for (int j = 0; j < 6; ++j) s += T(RK_E[j]) * K[j * ko + ho];
                         const T m = fabs(pn) > fabs(p[c]) ? fabs(pn) : fabs(p[c]);
-                        const T r = fabs(h * s) / (T(a.rk->atol) + T(a.rk->rtol) * m);
+                        const T r = rk_scaled(h * s, T(a.rk->atol) + T(a.rk->rtol) * m);
                         rkerr = r > rkerr ? r : rkerr;
                         o[c] = p[c];               // P5 itself (for the spectrum)
                     }

@@ -455,7 +455,7 @@ __global__ void __launch_bounds__(UpdMaxThreads<T>::v)
                             acc += T(RK_E[j]) * K[j * ko + c * comp + ho];
                         const T sc = T(a.rk->atol) +
                                      T(a.rk->rtol) * (fabs(pn) > fabs(p[c]) ? fabs(pn) : fabs(p[c]));
-                        const T r = fabs(h * acc) / sc;
+                        const T r = rk_scaled(h * acc, sc);
                         rkerr = r > rkerr ? r : rkerr;
                         o[c] = p[c];                             // P5 itself (for the spectrum)
                     }
