@@ -1080,9 +1080,9 @@ static hipError_t plane_impl(const Geom &g, void *S1, const void *Nt, const void
     const size_t shm = plane_lds_bytes<T, MY, MZ>(g.nz);
     if (shm > lds_max) return hipErrorInvalidConfiguration;
     if (query) {
-        if (shm > 65536)
+        if (lds_max > 65536)     // the device's limit: contexts of other heights share the kernel
             return hipFuncSetAttribute((const void *)k_plane<T, MY, MZ>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
         return hipSuccess;
     }
     hipLaunchKernelGGL((k_plane<T, MY, MZ>), dim3(g.hx * g.nb), dim3(C::NTHR), shm, s,

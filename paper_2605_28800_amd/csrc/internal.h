@@ -173,7 +173,7 @@ int update_rows_per_block(int prec, const Geom &g, bool step);
 // the two-kernel evaluation (slab.hip); UpdArgs as for launch_update, the slab
 // spectra from S1 on into S2 behind it
 bool slab_fits(const Geom &g);
-hipError_t prepare_slab(int prec, const Geom &g);
+hipError_t prepare_slab(int prec, const Geom &g, size_t lds_max);
 hipError_t launch_slab(int prec, int mode, const Geom &g, const UpdArgs &a, const void *tw,
                        hipStream_t s);
 hipError_t launch_ymul(int prec, const Geom &g, void *S, const void *Nt, const void *tw,

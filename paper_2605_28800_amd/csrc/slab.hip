@@ -541,14 +541,18 @@ static size_t slab_lds(const Geom &g)
 
 template <typename T, int M, int MODE>
 static hipError_t slab_one(const Geom &g, const UpdArgs &a, const void *tw, hipStream_t s,
-                           bool prepare)
+                           bool prepare, size_t lds_max)
 {
     const size_t shm = slab_lds<T, M>(g);
-    if (prepare)
-        return shm <= 65536 ? hipSuccess
-                            : hipFuncSetAttribute((const void *)k_slab<T, M, MODE>,
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                  (int)shm);
+    if (prepare) {
+        // the limit belongs to the kernel, which contexts of other heights share:
+        // the device's, not this grid's
+        if (shm > lds_max) return hipErrorInvalidConfiguration;
+        return lds_max <= 65536 ? hipSuccess
+                                : hipFuncSetAttribute((const void *)k_slab<T, M, MODE>,
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                      (int)lds_max);
+    }
     UpdArgs am = a;
     const unsigned n = (unsigned)(g.ny * g.nb);
     am.mgx = div_magic((unsigned)g.ny, n);
@@ -559,32 +563,32 @@ static hipError_t slab_one(const Geom &g, const UpdArgs &a, const void *tw, hipS
 
 template <typename T, int M>
 static hipError_t slab_mode(int mode, const Geom &g, const UpdArgs &a, const void *tw,
-                            hipStream_t s, bool prepare)
+                            hipStream_t s, bool prepare, size_t lds_max)
 {
     switch (mode) {
-    case UPD_STEP: return slab_one<T, M, UPD_STEP>(g, a, tw, s, prepare);
-    case UPD_FIELD: return slab_one<T, M, UPD_FIELD>(g, a, tw, s, prepare);
-    case UPD_ENERGY: return slab_one<T, M, UPD_ENERGY>(g, a, tw, s, prepare);
-    case UPD_STEP_MS: return slab_one<T, M, UPD_STEP_MS>(g, a, tw, s, prepare);
-    case UPD_STEP_RK: return slab_one<T, M, UPD_STEP_RK>(g, a, tw, s, prepare);
-    default: return slab_one<T, M, UPD_FX>(g, a, tw, s, prepare);
+    case UPD_STEP: return slab_one<T, M, UPD_STEP>(g, a, tw, s, prepare, lds_max);
+    case UPD_FIELD: return slab_one<T, M, UPD_FIELD>(g, a, tw, s, prepare, lds_max);
+    case UPD_ENERGY: return slab_one<T, M, UPD_ENERGY>(g, a, tw, s, prepare, lds_max);
+    case UPD_STEP_MS: return slab_one<T, M, UPD_STEP_MS>(g, a, tw, s, prepare, lds_max);
+    case UPD_STEP_RK: return slab_one<T, M, UPD_STEP_RK>(g, a, tw, s, prepare, lds_max);
+    default: return slab_one<T, M, UPD_FX>(g, a, tw, s, prepare, lds_max);
     }
 }
 
 static hipError_t slab_any(int prec, int mode, const Geom &g, const UpdArgs &a, const void *tw,
-                           hipStream_t s, bool prepare)
+                           hipStream_t s, bool prepare, size_t lds_max)
 {
     if (prec == PREC_F32) {
-        TDGL_SLAB_MX(return (slab_mode<float, LEN_>(mode, g, a, tw, s, prepare)))
+        TDGL_SLAB_MX(return (slab_mode<float, LEN_>(mode, g, a, tw, s, prepare, lds_max)))
     } else {
-        TDGL_SLAB_MX(return (slab_mode<double, LEN_>(mode, g, a, tw, s, prepare)))
+        TDGL_SLAB_MX(return (slab_mode<double, LEN_>(mode, g, a, tw, s, prepare, lds_max)))
     }
 }
 
 hipError_t launch_slab(int prec, int mode, const Geom &g, const UpdArgs &a, const void *tw,
                        hipStream_t s)
 {
-    return slab_any(prec, mode, g, a, tw, s, false);
+    return slab_any(prec, mode, g, a, tw, s, false, 0);
 }
 
 template <typename T, int MY>
@@ -608,11 +612,11 @@ hipError_t launch_ymul(int prec, const Geom &g, void *S, const void *Nt, const v
     }
 }
 
-hipError_t prepare_slab(int prec, const Geom &g)
+hipError_t prepare_slab(int prec, const Geom &g, size_t lds_max)
 {
     const int modes[6] = {UPD_STEP, UPD_FIELD, UPD_ENERGY, UPD_STEP_MS, UPD_STEP_RK, UPD_FX};
     for (int m : modes) {
-        const hipError_t e = slab_any(prec, m, g, UpdArgs{}, nullptr, nullptr, true);
+        const hipError_t e = slab_any(prec, m, g, UpdArgs{}, nullptr, nullptr, true, lds_max);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -382,7 +382,8 @@ constexpr int PLANE_POINTS = 512;
 
 void choose_path(tdgl_ctx *c)
 {
-    c->use_slab = c->fft_path == 0 && slab_fits(c->g) && prepare_slab(c->prec, c->g) == hipSuccess;
+    c->use_slab = c->fft_path == 0 && slab_fits(c->g) &&
+                  prepare_slab(c->prec, c->g, c->lds_max) == hipSuccess;
     c->use_plane = !c->use_slab && c->fft_path == 0 && c->g.nz * c->g.my <= PLANE_POINTS &&
                    launch_plane(c->prec, c->g, nullptr, nullptr, nullptr, c->lds_max, nullptr,
                                 true) == hipSuccess;
