@@ -101,9 +101,10 @@ struct tdgl_ctx {
     void *P[2]{};
     void *S1 = nullptr, *S2 = nullptr, *Nt = nullptr, *coef = nullptr, *kp = nullptr;
     void *twf = nullptr, *twd = nullptr;
-    double *gl = nullptr, *partials = nullptr, *res = nullptr;
+    double *gl = nullptr;         // quadrature tables, from the first tensor build on
+    double *partials = nullptr, *res = nullptr;
     void *rlx = nullptr;          // relaxation bookkeeping (tdgl_relax)
-    RkState *rk = nullptr;        // RK45 controller
+    RkState *rk = nullptr;        // RK45 controller, in the memory of res
     int *flag = nullptr;
     int cur = 0;
     int yt = 2;                   // rows per group of the update kernel: steps, field
@@ -152,7 +153,7 @@ tdgl_status fail(tdgl_ctx *c, tdgl_status st, const char *fmt, ...)
 
 // ---- layout of the device workspace
 struct Layout {
-    size_t P, S1, S2, Nt, coef, kp, twf, twd, gl, partials, flag, res, rlx, rk;
+    size_t P, S1, S2, Nt, coef, kp, twf, twd, partials, flag, res, rlx;
     size_t xbuf, extra, total;     // cross-term field; history or RK45 buffers
 };
 
@@ -181,12 +182,12 @@ Layout layout_of(const tdgl_ctx *c, int scheme)
     L.kp = take(sizeof(KParams<double>));
     L.twf = take((size_t)TW_ENTRIES * 2 * sizeof(float));
     L.twd = take((size_t)TW_ENTRIES * 2 * sizeof(double));
-    L.gl = take((size_t)GL_ENTRIES * sizeof(double));
     L.partials = take((size_t)c->nblocks * g.nb * 8 * sizeof(double));
     L.flag = take(sizeof(int));
-    L.res = take((size_t)8 * g.nb * sizeof(double));
+    // results of the reductions; tdgl_step keeps the RK45 controller here while
+    // it runs, when nothing reduces energies
+    L.res = take(std::max((size_t)8 * g.nb * sizeof(double), rk_bytes(g.nb)));
     L.rlx = take(RLX_BYTES_PER_INSTANCE * g.nb + 32);
-    L.rk = take(rk_bytes(g.nb));
     const size_t pbytes = 3 * N * c->esz;
     L.xbuf = take(pbytes);
     L.extra = off;
@@ -205,6 +206,7 @@ void gauss_legendre(int n, long double *x, long double *w)
         long double u = cosl(3.14159265358979323846264338327950288L * (i + 0.75L) / (n + 0.5L));
         long double dp = 1.0L;
         for (int it = 0; it < 50; ++it) {
+            const long double u0 = u;
             long double p0 = 1.0L, p1 = u;
             for (int k = 2; k <= n; ++k) {
                 const long double p2 = ((2 * k - 1) * u * p1 - (k - 1) * p0) / k;
@@ -213,6 +215,7 @@ void gauss_legendre(int n, long double *x, long double *w)
             }
             dp = n * (u * p1 - p0) / (u * u - 1.0L);
             u -= p1 / dp;
+            if (fabsl(u - u0) < 1e-18L) break;
         }
         x[i] = 0.5L * (u + 1.0L);
         w[i] = 1.0L / ((1.0L - u * u) * dp * dp);
@@ -224,9 +227,10 @@ void gauss_legendre(int n, long double *x, long double *w)
 // u p_k - b_k p_{k-1} of the even weight come from their defining inner
 // products (Stieltjes' procedure; an inner product of polynomials of total
 // degree below 2 GL_MAXN is exact with GL_MAXN + 1 Legendre nodes on each half),
-// the roots by bisection between those of the previous polynomial, the
-// weights as 1 / sum of the squared orthonormal polynomials; in long double.
-void quadrature_tables(double *tab)
+// the roots by Newton's method from the middle between those of the previous
+// polynomial, which part them (a step out of that interval becomes a bisection),
+// the weights as 1 / sum of the squared orthonormal polynomials; in long double.
+void make_quadrature_tables(double *tab)
 {
     typedef long double ld;
     constexpr int Q = GL_MAXN + 1;
@@ -243,13 +247,16 @@ void quadrature_tables(double *tab)
     }
     gauss_legendre(Q, gx, gw);
     ld b[GL_MAXN] = {0}, norm[GL_MAXN];           // b_k and |p_k|^2
-    auto eval = [&](int n, ld x) {                // p_n(x)
-        ld p0 = 0, p1 = 1;
+    auto eval = [&](int n, ld x, ld *slope = nullptr) {          // p_n(x)
+        ld p0 = 0, p1 = 1, d0 = 0, d1 = 0;
         for (int k = 0; k < n; ++k) {
-            const ld p2 = x * p1 - (k ? b[k] * p0 : 0);
+            const ld p2 = x * p1 - (k ? b[k] * p0 : 0), d2 = x * d1 + p1 - (k ? b[k] * d0 : 0);
             p0 = p1;
             p1 = p2;
+            d0 = d1;
+            d1 = d2;
         }
+        if (slope) *slope = d1;
         return p1;
     };
     for (int k = 0; k < GL_MAXN; ++k) {
@@ -266,24 +273,41 @@ void quadrature_tables(double *tab)
         for (int i = 0; i < n; ++i) {
             ld lo = i == 0 ? -1 : prev[i - 1], hi = i == n - 1 ? 1 : prev[i];
             const bool up = eval(n, lo) < 0;
+            ld x = 0.5L * (lo + hi);
             for (int it = 0; it < 70; ++it) {
-                const ld mid = 0.5L * (lo + hi);
-                if ((eval(n, mid) < 0) == up) lo = mid;
-                else hi = mid;
+                ld slope;
+                const ld v = eval(n, x, &slope), x0 = x;
+                if ((v < 0) == up) lo = x;
+                else hi = x;
+                x -= v / slope;
+                if (!(x >= lo && x <= hi)) x = 0.5L * (lo + hi);
+                else if (fabsl(x - x0) < 1e-12L) break;     // (a step squares the error)
             }
-            root[i] = 0.5L * (lo + hi);
+            root[i] = x;
         }
         for (int i = 0; i < n; ++i) {
             prev[i] = root[i];
-            ld s = 0;
-            for (int k = 0; k < n; ++k) {
-                const ld v = eval(k, root[i]);
-                s += v * v / norm[k];
+            ld s = 0, p0 = 0, p1 = 1;
+            for (int k = 0; k < n; ++k) {         // p1 = p_k(root)
+                s += p1 * p1 / norm[k];
+                const ld p2 = root[i] * p1 - (k ? b[k] * p0 : 0);
+                p0 = p1;
+                p1 = p2;
             }
             t[n * GL_MAXN + i] = (double)root[i];
             w[n * GL_MAXN + i] = (double)(1 / s);
         }
     }
+}
+
+// the tables, computed once per process and only for a tensor build (0.4 ms of
+// host time; the build of a small box takes as much)
+const double *quadrature_tables()
+{
+    static double tab[GL_ENTRIES];
+    static const bool made = (make_quadrature_tables(tab), true);
+    (void)made;
+    return tab;
 }
 
 // twiddles W_M^k = exp(-2 pi i k / M) for every power-of-two M, table of M at offset M
@@ -333,22 +357,18 @@ tdgl_status ensure_device(tdgl_ctx *c)
     c->kp = b + L.kp;
     c->twf = b + L.twf;
     c->twd = b + L.twd;
-    c->gl = reinterpret_cast<double *>(b + L.gl);
     c->partials = reinterpret_cast<double *>(b + L.partials);
     c->flag = reinterpret_cast<int *>(b + L.flag);
     c->res = reinterpret_cast<double *>(b + L.res);
     c->rlx = b + L.rlx;
-    c->rk = reinterpret_cast<RkState *>(b + L.rk);
+    c->rk = reinterpret_cast<RkState *>(c->res);
     c->xbuf = b + L.xbuf;
     if (c->scheme == TDGL_AB3M2) c->hist = b + L.extra;
     if (c->scheme == TDGL_RK45) c->rkbuf = b + L.extra;
     auto twf = twiddle_table<float>();
     auto twd = twiddle_table<double>();
-    std::vector<double> gl(GL_ENTRIES);
-    quadrature_tables(gl.data());
     HIP_TRY(c, hipMemcpy(c->twf, twf.data(), twf.size() * sizeof(float), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemcpy(c->twd, twd.data(), twd.size() * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(c->gl, gl.data(), gl.size() * sizeof(double), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemset(c->flag, 0, sizeof(int)));
     int dev = 0, optin = 0;
     HIP_TRY(c, hipGetDevice(&dev));
@@ -938,6 +958,7 @@ void tdgl_destroy(tdgl_ctx *c)
         if (c->hist && c->hist_own) (void)hipFree(c->hist);
         if (c->rkbuf && c->rk_own) (void)hipFree(c->rkbuf);
         if (c->xbuf && c->x_own) (void)hipFree(c->xbuf);
+        if (c->gl) (void)hipFree(c->gl);
         if (c->cap) (void)hipStreamDestroy(c->cap);
     }
     delete c;
@@ -1050,6 +1071,19 @@ tdgl_status tdgl_build_tensor(tdgl_ctx *c, int mimg)
     const Geom &g = c->g;
     const size_t nreal = (size_t)g.mx * g.my * g.mz;
     const size_t ncplx = (size_t)g.mz * g.my * g.hx;
+    if (!c->gl) {
+        if (hipMalloc(&c->gl, GL_ENTRIES * sizeof(double)) != hipSuccess) {
+            c->gl = nullptr;
+            return fail(c, TDGL_E_NOMEM, "tensor build: hipMalloc failed");
+        }
+        const hipError_t e = hipMemcpy(c->gl, quadrature_tables(), GL_ENTRIES * sizeof(double),
+                                       hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(c->gl);
+            c->gl = nullptr;
+            return fail(c, TDGL_E_HIP, "tensor build: %s", hipGetErrorString(e));
+        }
+    }
     double *R = nullptr;
     void *C = nullptr;
     if (hipMalloc(&R, 6 * nreal * sizeof(double)) != hipSuccess)
