@@ -246,10 +246,11 @@ tdgl_status tdgl_set_graph_chunk(tdgl_ctx *ctx, int steps);
  * with power-of-two transforms in two kernels (x and z passes with the update,
  * y passes with the tensor multiply), fuses the y pass, the z pass with the
  * tensor multiply and the inverse y pass into one kernel per kx plane when
- * that plane is small (at most 512 points per component), and uses three
- * kernels otherwise; path 1 always uses the three kernels.  Results agree to
- * rounding.  tdgl_get_fft_path reports whether a fused evaluation is in use
- * (known after the first call that touches the device). */
+ * that plane is small (at most 512 points per component, or 1024 where a batch
+ * has about as many planes as the device CUs), and uses three kernels
+ * otherwise; path 1 always uses the three kernels.  Results agree to rounding.
+ * tdgl_get_fft_path reports whether a fused evaluation is in use (known after
+ * the first call that touches the device). */
 tdgl_status tdgl_set_fft_path(tdgl_ctx *ctx, int path);
 tdgl_status tdgl_get_fft_path(const tdgl_ctx *ctx, int *fused);
 
@@ -422,8 +423,8 @@ tdgl_status tdgl_profile_step(tdgl_ctx *ctx, int nsteps, double ms_out[5]);
 tdgl_status tdgl_profile_kernels(tdgl_ctx *ctx, int nrep, double ms_out[5]);
 
 /* Pick the fastest launch configuration for this context by measurement:
- * each candidate (the fused evaluation where there is one or the three passes,
- * times update tiles of 2, 4, 8, 16 rows where they apply; then, for the three passes, the
+ * each candidate (the fused evaluations that fit or the three passes, times
+ * update tiles of 2, 4, 8, 16 rows where they apply; then, for the three passes, the
  * z-pass tiles of 64, 128 and 256 bytes with the rows found; last, the
  * other store mode) advances the current state by nsteps steps as one
  * graph, once to warm up and once timed with HIP events, always from the

@@ -261,6 +261,12 @@ struct IdxPad {         // contiguous line, one pad slot after every 8 elements
     __device__ __forceinline__ int shift(int d) const { return d + (d >> 3); }
     __device__ __forceinline__ int near(int d) const { return d; }
 };
+// the y passes' lines: the compiler fuses alike in k_rowb and k_plane but for FP32
+// lines of 32 points, whose order is therefore written out
+template <typename T, int M>
+struct IdxPadY : IdxPad {
+    static constexpr bool FIX = sizeof(T) == 4 && M == 32;
+};
 struct IdxStridePad {   // lines interleaved at stride s, one pad row after every 8
     int s;              // elements: 64 lanes of 8-byte accesses hit the minimum of
                         // two LDS bank cycles in every radix stage

@@ -179,8 +179,8 @@ __global__ void k_rowb(const cpx<T> *in, cpx<T> *out, int hx, unsigned R, unsign
     }
     // a line's lanes (KB * TPL of them) lie within one wave where 4 TPL <= 64:
     // its stages then need wave-level barriers only
-    fft_line<T, M, INV, IdxPad, KB * TPL <= 64>(v, lds + (l < lpw ? l : 0) * LEN, IdxPad{}, t, tr,
-                                                act);
+    fft_line<T, M, INV, IdxPadY<T, M>, KB * TPL <= 64>(v, lds + (l < lpw ? l : 0) * LEN,
+                                                       IdxPadY<T, M>{}, t, tr, act);
     cpx<T> *dst = out + (act ? (INV ? b1 : b2) : 0);
     if (nt) {
 #pragma unroll
@@ -271,8 +271,8 @@ __device__ __forceinline__ void tensor_row(const T *__restrict__ Nt, int kx, int
     n2 = b[r.i2 * qs] * odd_sign(r.i2, sy, sz);
 }
 
-// one component of the product, in a fixed order of roundings: both z passes
-// give the same bits
+// one component of the product, in a fixed order of roundings: both z passes and
+// the plane pass give the same bits
 template <typename T>
 __device__ __forceinline__ cpx<T> dot3(T n0, cpx<T> a, T n1, cpx<T> b, T n2, cpx<T> c)
 {
@@ -605,7 +605,7 @@ __global__ void __launch_bounds__((PlaneCfg<T, MY, MZ>::NTHR))
     const int tid = threadIdx.x;
     const int kx = blockIdx.x / nb;          // work-group = plane (kx, instance)
     if (frozen && frozen[blockIdx.x % nb]) return;
-    const IdxPad pad{};
+    const IdxPadY<T, MY> pad{};
     const int nlines = 3 * nz;
     // row (line, y) of this plane in the KB-blocked S1: stride KB
     const int bi = blockIdx.x - kx * nb;
@@ -677,7 +677,7 @@ __global__ void __launch_bounds__((PlaneCfg<T, MY, MZ>::NTHR))
             const cpx<T> p1 = zs[1 * LZ * CK + ipz(kz) + cc];
             const cpx<T> p2 = zs[2 * LZ * CK + ipz(kz) + cc];
             const T n0 = nrow[q][0], n1 = nrow[q][1], n2 = nrow[q][2];
-            v[q] = {n0 * p0.x + n1 * p1.x + n2 * p2.x, n0 * p0.y + n1 * p1.y + n2 * p2.y};
+            v[q] = dot3(n0, p0, n1, p1, n2, p2);
         }
         __syncthreads();
         fft_line<T, MZ, true>(v, L, ipz, tz, twz_r, true);

@@ -218,3 +218,7 @@ hipError_t launch_tensor_octant(int prec, const Geom &g, const void *C, double s
                                 hipStream_t s);
 
 }  // namespace tdgl
+
+// for tests: the evaluation in use, 0 three passes, 1 fused plane pass, 2 two kernels
+// (known after the first call that touches the device)
+extern "C" int tdgl_internal_eval_path(const struct tdgl_ctx *c);

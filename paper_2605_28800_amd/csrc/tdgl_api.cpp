@@ -120,7 +120,8 @@ struct tdgl_ctx {
     int hist_count = 0;           // valid history entries (0..2)
     int hist_pos = 0;             // buffer of the newest entry
     size_t lds_max = 65536;      // dynamic LDS one work-group may use on this device
-    int fft_path = 0;            // 0: fused plane pass when it fits, 1: three passes
+    int fft_path = 0;            // 0: the built-in rule (choose_path), 1: three passes, 2 (by
+                                 // tdgl_autotune): the plane pass where it fits
     int ztile = 0;               // z-pass column tile, bytes per z row (0: built-in choice)
     bool use_plane = false;      // the fused plane pass
     bool use_slab = false;       // the two-kernel evaluation (slab.hip), spectra in S1 and S2
@@ -389,22 +390,49 @@ tdgl_status ensure_device(tdgl_ctx *c)
 
 const void *tw(const tdgl_ctx *c) { return c->prec == PREC_F32 ? c->twf : c->twd; }
 
-// The fused plane pass is used for planes of at most PLANE_POINTS (z, ky)
-// points per component that fit in the LDS of one work-group.  One group holds
-// a whole plane, so larger ones leave few waves per CU; smaller ones are
-// cheaper than two more launches.  Heun steps, fused against three passes:
-// 8x8x8 (128 points) 25.1 / 28.4 us, 32x32x8 film (256) 27.2 / 30.4, 32x32x8
-// box FP64 (512) 33.4 / 33.6; 100x30x12 box (768) 47.5 / 42.0, 64x64x16 film
-// (1024) 41.0 / 36.0, 75x50x21 box (2688) 126 / 83, 24 boxes of 32x32x32 (2048)
-// 212 / 148.  The rule does not look at the batch, so that an instance
-// rounds as it does alone.
-constexpr int PLANE_POINTS = 512;
+// Where the fused plane pass is used.  One group holds a whole plane of (z, ky)
+// points per component, so it takes the same time for any number of groups
+// (planes times instances) up to one per CU, twice that for the next one, and the
+// longer the larger the plane; three passes grow with the spectra, from two more
+// launches on.  Heun steps, fused / three passes:
+//   at most 512 points: one box 8x8x8 (128 points) 25.1 / 28.4 us, 32x32x8 film
+//     (256) 27.2 / 30.4, 8x4x40 FP32 (320) 25.4 / 33.7, 64 of them 57 / 66, 32x32x8 box
+//     FP64 (512) 33.4 / 33.6
+//   one box above, few groups: 16x16x20 FP64 (640 points, 17 groups) 41.6 / 33.7,
+//     100x30x12 (768, 129) 47.5 / 42.0, 64x64x16 film (1024, 65) 41.0 / 36.0
+//   batches of up to 256 groups: 8 of 20x30x11 FP32 (704 points, 200 groups) 41.1 /
+//     48.7, FP64 50.2 / 69.0; 3 of 64x64x8 (1024, 195) 50.4 / 52.3, 70.8 / 75.7; 16 of
+//     12x16x24 (768, 208) 40.3 / 47.0, 59.2 / 72.8; below about 180 (FP32) or 150
+//     (FP64) groups they lose: 4 of 32x32x9 FP32 (132) 39.2 / 37.1; with instances in
+//     multiples of the 8 XCDs, each of which then reads one instance's planes, from
+//     100 on: 8 of 16x16x32 (136) 37.2 / 42.7, 49.3 / 62.5; 7 of them (119) 43.5 / 42.1
+//   the longest z transforms, of which the passes are dear: 8 of 8x8x60 (960 points, 72
+//     groups) 34.0 / 39.6, 47.9 / 52.3; the shortest, in boxes with wide planes:
+//     120x120x3 (768, 129) 42.2 / 45.3, 53.3 / 59.8
+//   more groups than CUs: 8 of 32x32x9 FP32 (576 points, 264) 57.4 / 45.7; FP64, where
+//     the passes take longer, up to a few more: 75.0 / 76.7, 8 of 30x30x10 75.8 / 81.8,
+//     but 4 of 60x60x5 (260, no multiple of 8) 83.8 / 71.8
+//   larger planes: 8 of 8x60x12 (1536, 72) 53.0 / 42.5, 75x50x21 box (2688) 126 / 83
+// Both round alike, so that an instance of a batch keeps its bits.
+bool plane_wins(int prec, const Geom &g)
+{
+    const int points = g.nz * g.my;
+    const long long groups = (long long)g.hx * g.nb;
+    if (points <= 512) return true;
+    const bool xcd = g.nb % 8 == 0;
+    const bool more = prec == PREC_F64 && xcd && (g.mz == 16 || g.mz == 32);
+    if (points > 1024 || groups > (more ? 288 : 256)) return false;
+    if (g.mz >= 128) return groups >= (xcd ? 64 : 100);
+    if (g.mz == 8) return groups >= 128;
+    return groups >= (xcd ? 100 : (prec == PREC_F32 ? 180 : 150));
+}
 
 void choose_path(tdgl_ctx *c)
 {
     c->use_slab = c->fft_path == 0 && slab_fits(c->g) &&
                   prepare_slab(c->prec, c->g, c->lds_max) == hipSuccess;
-    c->use_plane = !c->use_slab && c->fft_path == 0 && c->g.nz * c->g.my <= PLANE_POINTS &&
+    c->use_plane = !c->use_slab &&
+                   (c->fft_path == 2 || (c->fft_path == 0 && plane_wins(c->prec, c->g))) &&
                    launch_plane(c->prec, c->g, nullptr, nullptr, nullptr, c->lds_max, nullptr,
                                 true) == hipSuccess;
 }
@@ -1279,6 +1307,11 @@ tdgl_status tdgl_get_z_tile(const tdgl_ctx *c, int *row_bytes)
     return TDGL_OK;
 }
 
+int tdgl_internal_eval_path(const tdgl_ctx *c)
+{
+    return !c ? -1 : c->use_slab ? 2 : (c->use_plane ? 1 : 0);
+}
+
 tdgl_status tdgl_get_fft_path(const tdgl_ctx *c, int *fused)
 {
     if (!c || !fused) return TDGL_E_ARG;
@@ -2141,10 +2174,14 @@ tdgl_status tdgl_autotune(tdgl_ctx *c, int nsteps, int choice[2], double *ms_per
         *ms_step = ms / nsteps;
         return true;
     };
-    for (int path = 0; path <= 1 && he == hipSuccess && rs == TDGL_OK; ++path) {
+    bool plane_tried = false;
+    for (int path : {0, 2, 1}) {
+        if (he != hipSuccess || rs != TDGL_OK) break;
         c->fft_path = path;
         choose_path(c);
-        if (path == 0 && !fused(c)) continue;       // no fused evaluation for this grid
+        if (path != 1 && !fused(c)) continue;       // no fused evaluation for this grid
+        if (path == 2 && plane_tried) continue;
+        plane_tried = c->use_plane;
         for (int yt = 2; yt <= 16 && he == hipSuccess && rs == TDGL_OK; yt *= 2) {
             if (((c->g.ny + yt - 1) / yt) * c->g.nz > nb_groups) continue;
             if (yt > 2 && yt > c->g.ny + (c->g.ny & 1)) break;
