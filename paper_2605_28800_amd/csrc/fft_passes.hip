@@ -148,8 +148,21 @@ __global__ void k_row(const cpx<T> *in, cpx<T> *out, long long nlines, long long
 // Forward: S1 -> S2; inverse: S2 -> S1.  The KB lines of one block sit in
 // adjacent lanes, so that every load and store of a wave is contiguous.
 // Lines of kx >= hx (the padding of the last block) are idle.
+// Threads of a group: 128 as the plain row pass, but at least one block of KB
+// lines.  Told to the compiler for the FP64 lines of twelve points a thread, which
+// spill in the 128 registers that groups of 1024 threads would leave (68 bytes
+// a lane at 192 points): y passes of 90x90x20 FP64 10.3 and 11.4 -> 7.6 and 7.0 us,
+// of 6 boxes of 90x90x8 23.5 and 24.8 -> 17.1 and 16.0.  Lines without spills keep
+// the default: FP32 at 384 points was 1.5 % slower with it.
+template <typename T, int M>
+struct RowbCfg {
+    static constexpr int TPL = Plan<M>::TPL;
+    static constexpr int LPW = TPL >= 128 / KB ? KB : 128 / TPL;     // lines per group
+    static constexpr int BOUND = sizeof(T) == 8 && M % 3 == 0 ? LPW * TPL : 1024;
+};
+
 template <typename T, int M, bool INV, bool HALF>
-__global__ void k_rowb(const cpx<T> *in, cpx<T> *out, int hx, unsigned R, unsigned mR, int ny,
+__global__ void __launch_bounds__((RowbCfg<T, M>::BOUND)) k_rowb(const cpx<T> *in, cpx<T> *out, int hx, unsigned R, unsigned mR, int ny,
                        int my, int n_in, int n_out, const cpx<T> *__restrict__ tw, int lpw,
                        Freeze fz, int nt)
 {
@@ -845,8 +858,7 @@ hipError_t prepare_fx(int prec, int M)
 template <typename T, int M>
 static hipError_t rowb_prepare()
 {
-    constexpr int TPL = Plan<M>::TPL;
-    constexpr int lpw = TPL >= 128 / KB ? KB : 128 / TPL;
+    constexpr int lpw = RowbCfg<T, M>::LPW;
     constexpr size_t shm = (size_t)lpw * LinePad<M>::len * sizeof(cpx<T>);
     if (shm <= 65536) return hipSuccess;
     const void *f[4] = {(const void *)k_rowb<T, M, false, false>,
@@ -866,11 +878,9 @@ static hipError_t rowb_impl(bool inv, const void *S1, void *S2, int hx, long lon
                             int my, int n_in, int n_out, const void *tw, hipStream_t s,
                             Freeze fz, int nt)
 {
-    constexpr int TPL = Plan<M>::TPL;
-    // 128-thread groups as the plain row pass, but at least one block of KB lines
     // (above 64 KiB of LDS, i.e. 1024-point FP64 lines, rowb_prepare has
     // raised the kernels' limit)
-    const int lpw = TPL >= 128 / KB ? KB : 128 / TPL;
+    constexpr int TPL = RowbCfg<T, M>::TPL, lpw = RowbCfg<T, M>::LPW;
     const long long rows = (long long)hx_blocked(hx) / KB * R;      // line blocks
     const long long blocks = (rows + lpw / KB - 1) / (lpw / KB);
     if (blocks <= 0) return hipSuccess;
