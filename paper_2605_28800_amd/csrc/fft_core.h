@@ -13,7 +13,7 @@
 // W_{PR}^{rk}, R-point DFT, outputs to y[(i-k) R + k + r P].  The first stage
 // (P = 1) needs no twiddles and reads the registers; the last stage
 // (P R = M) writes y[i + r M/R], which is again the register layout.
-// Radices: 8, 4, 2 for powers of two; 4, 2 and a last 12 otherwise.
+// Radices: 8, 4, 2 for powers of two; 4, 2 and a last 12 (or 3) otherwise.
 //
 // Forward transforms use W = exp(-2 pi i/M); inverse transforms the
 // conjugate, unnormalised.
@@ -239,6 +239,7 @@ __device__ __forceinline__ void dftR(cpx<T> *v)
     else if constexpr (R == 8 && FIX) dft8_fix<T, INV>(v);
     else if constexpr (R == 8) dft8<T, INV>(v);
     else if constexpr (R == 4) dft4<T, INV>(v);
+    else if constexpr (R == 3) dft3<T, INV>(v);
     else dft2<T, INV>(v);
 }
 
@@ -285,19 +286,22 @@ struct LinePad {
 // radix 8 while at least 8 points remain, then 4 or 2.  M = 3 * 2^a (a >= 2):
 // twelve points per thread, radix 4 while 48 or more remain, one radix 2
 // where 24 remain, and a last radix-12 stage in registers, so that every stage
-// before the last has a power-of-two span P.  (Radices 4, 2 and a last 3 take
-// one more exchange through LDS for every length: Heun steps of 48x40x12 45.5 us
-// against 41.6 FP32, 54.1 / 50.7 FP64; of 190x180x20 225 / 208 and 386 / 365; of 16
-// boxes of 96x96x8 FP32 223 / 219; only 10x11x6 is no faster, 35.5 / 36.0 FP64.)
+// before the last has a power-of-two span P.  (Radices 4, 2 and a last 3, R12 =
+// false, take one more exchange through LDS for every length: Heun steps of 48x40x12
+// 45.5 us against 41.6 FP32, 54.1 / 50.7 FP64; of 190x180x20 225 / 208 and 386 / 365; of
+// 16 boxes of 96x96x8 FP32 223 / 219.  Only y passes of 24 points are faster with
+// them, FP64 ones (12x10x6: 3.2 and 3.2 us against 4.0 and 3.3, a step 33.8 / 35.4) and half
+// filled FP32 ones (6 of 16x12x4, a step 32.4 / 33.5).)
 template <int M>
 struct Plan {
     static constexpr bool R3 = M % 3 == 0;
     static constexpr int PPT = R3 ? 12 : 8;    // points per thread
     static constexpr int TPL = M / PPT;        // threads per line
-    static constexpr int radix(int P)
+    static constexpr int radix(int P, bool r12)
     {
         return !R3 ? (M / P >= 8 ? 8 : M / P)
-                   : (M / P == 12 ? 12 : (M / P == 24 ? 2 : 4));
+               : r12 ? (M / P == 12 ? 12 : (M / P == 24 ? 2 : 4))
+                     : (M / P == 3 ? 3 : (M / P % 12 == 0 ? 4 : 2));
     }
 };
 
@@ -306,41 +310,41 @@ struct Plan {
 // twiddles per stage s >= 1; they depend only on the thread's position, so
 // a kernel loads them into registers at its start (TwReg), overlapping their
 // latency with the data loads, and the stages read them from registers.
-template <int M, int S>
+template <int M, int S, bool R12>
 struct Stage {
-    using Prev = Stage<M, (S > 0 ? S - 1 : 0)>;
+    using Prev = Stage<M, (S > 0 ? S - 1 : 0), R12>;
     static constexpr int P = S == 0 ? 1 : Prev::P * Prev::R;
-    static constexpr int R = Plan<M>::radix(P);
+    static constexpr int R = Plan<M>::radix(P, R12);
     static constexpr int NB = Plan<M>::PPT / R;
     static constexpr int NTW = S == 0 ? 0 : NB * (R - 1);
     static constexpr int OFF = S == 0 ? 0 : Prev::OFF + Prev::NTW;
     static constexpr bool LAST = P * R == M;
 };
-template <int M>
-struct Stage<M, 0> {
-    static constexpr int P = 1, R = Plan<M>::radix(1), NB = Plan<M>::PPT / R, NTW = 0, OFF = 0;
+template <int M, bool R12>
+struct Stage<M, 0, R12> {
+    static constexpr int P = 1, R = Plan<M>::radix(1, R12), NB = Plan<M>::PPT / R, NTW = 0, OFF = 0;
     static constexpr bool LAST = (R == M);
 };
 
-template <int M, int S = 0>
+template <int M, bool R12, int S = 0>
 constexpr int twiddle_count()
 {
-    if constexpr (Stage<M, S>::LAST) return Stage<M, S>::OFF + Stage<M, S>::NTW;
-    else return twiddle_count<M, S + 1>();
+    if constexpr (Stage<M, S, R12>::LAST) return Stage<M, S, R12>::OFF + Stage<M, S, R12>::NTW;
+    else return twiddle_count<M, R12, S + 1>();
 }
 
-template <typename T, int M>
+template <typename T, int M, bool R12 = true>
 struct TwReg {
-    static constexpr int N = twiddle_count<M>();
+    static constexpr int N = twiddle_count<M, R12>();
     cpx<T> w[N > 0 ? N : 1];
 };
 
-template <typename T, int M, int S = 1>
-__device__ __forceinline__ void twiddle_load(TwReg<T, M> &tr, const cpx<T> *__restrict__ tab,
+template <typename T, int M, int S = 1, bool R12>
+__device__ __forceinline__ void twiddle_load(TwReg<T, M, R12> &tr, const cpx<T> *__restrict__ tab,
                                              int t)
 {
-    if constexpr (!Stage<M, 0>::LAST) {
-        using St = Stage<M, S>;
+    if constexpr (!Stage<M, 0, R12>::LAST) {
+        using St = Stage<M, S, R12>;
         constexpr int TPL = Plan<M>::TPL;
 #pragma unroll
         for (int b = 0; b < St::NB; ++b) {
@@ -371,11 +375,11 @@ __device__ __forceinline__ void line_sync()
 
 // Stages s >= 1.  Every thread of the work-group (WAVE: of the wave) must
 // reach these barriers; threads with act == false only skip memory traffic.
-template <typename T, int M, int S, bool INV, class Idx, bool WAVE = false, class LT>
+template <typename T, int M, int S, bool INV, class Idx, bool WAVE = false, class LT, bool R12>
 __device__ __forceinline__ void fft_stages(cpx<T> (&v)[Plan<M>::PPT], LT *lds, Idx idx, int t,
-                                           const TwReg<T, M> &tr, bool act)
+                                           const TwReg<T, M, R12> &tr, bool act)
 {
-    using St = Stage<M, S>;
+    using St = Stage<M, S, R12>;
     constexpr int R = St::R, NB = St::NB, P = St::P;
     constexpr int PPT = Plan<M>::PPT, TPL = Plan<M>::TPL;
     constexpr int MR = M / R;
@@ -449,14 +453,14 @@ __device__ __forceinline__ void fft_stages(cpx<T> (&v)[Plan<M>::PPT], LT *lds, I
 // (barrier) before calling, and must barrier again before reusing it
 // afterwards.  tr: this thread's twiddles (twiddle_load with the forward
 // table; the inverse conjugates them).
-template <typename T, int M, bool INV, class Idx, bool WAVE = false, class LT>
+template <typename T, int M, bool INV, class Idx, bool WAVE = false, class LT, bool R12>
 __device__ __forceinline__ void fft_line(cpx<T> (&v)[Plan<M>::PPT], LT *lds, Idx idx, int t,
-                                         const TwReg<T, M> &tr, bool act)
+                                         const TwReg<T, M, R12> &tr, bool act)
 {
     static_assert(M >= 8 && M <= 1024 &&
                       ((M & (M - 1)) == 0 || (M % 3 == 0 && M >= 12 && ((M / 3) & (M / 3 - 1)) == 0)),
                   "length");
-    using S0 = Stage<M, 0>;
+    using S0 = Stage<M, 0, R12>;
     constexpr int R0 = S0::R, NB0 = S0::NB, TPL = Plan<M>::TPL;
     if constexpr (NB0 == 1) {
         // one radix-PPT butterfly over the thread's own elements

@@ -159,6 +159,10 @@ struct RowbCfg {
     static constexpr int TPL = Plan<M>::TPL;
     static constexpr int LPW = TPL >= 128 / KB ? KB : 128 / TPL;     // lines per group
     static constexpr int BOUND = sizeof(T) == 8 && M % 3 == 0 ? LPW * TPL : 1024;
+    // the last stage (Plan): radix 12, but for lines of 24 points that are FP64 or half
+    // filled: there it leaves six radix-2 butterflies a thread before it, with two
+    // accesses each, while radix 4 has three with four and drops the zero half earlier
+    static constexpr bool r12(bool half) { return M != 24 || (sizeof(T) == 4 && !half); }
 };
 
 template <typename T, int M, bool INV, bool HALF>
@@ -178,7 +182,7 @@ __global__ void __launch_bounds__((RowbCfg<T, M>::BOUND)) k_rowb(const cpx<T> *i
     const unsigned kxb = udiv(rb, R, mR), r = rb - kxb * R;
     const int kx = (int)kxb * KB + sub;
     const bool act = l < lpw && kx < hx && !fz.skip((long long)kx * R + r);
-    TwReg<T, M> tr;
+    TwReg<T, M, RowbCfg<T, M>::r12(HALF)> tr;
     twiddle_load(tr, tw, t);
     const long long b1 = (long long)rb * ny * KB + sub;     // S1 line
     const long long b2 = (long long)rb * my * KB + sub;     // S2 line
