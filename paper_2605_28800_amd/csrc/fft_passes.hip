@@ -1044,17 +1044,26 @@ int zmul_auto_tile(int prec, const Geom &g)
 //   FP64 mz <= 64, z half filled: 32x32x32 4 of them 10.5 / 10.4 (1152 waves), 12
 //     24.1 / 22.1 (3456), 128x128x16 16.2 / 15.9 (2112); otherwise the eight input rows
 //     of a component cost the second wave per SIMD: 60x60x10 4 of them 16.7 / 19.7
-//   mz = 128 (k_zmul: two groups of 12 waves per CU): FP32 8x8x40 6.7 / 6.5 (48 waves),
-//     32x32x64 9.0 / 7.7; FP64 8x8x40 6.4 / 7.4, 32x32x64 11.9 / 9.8 (576).  The FP32 tile
-//     is 32 bytes of each z row, which pays while the spectra stay in the 256 MB
-//     cache: 128x128x64 47 / 42 (105 MB), 200x200x64 171 / 245 (203 MB)
+//   mz = 128 (k_zmul: two groups of 12 waves per CU): FP32 8x8x40 6.6 / 6.5 (48 waves),
+//     78x6x57 6.9 / 7.5 (400), 32x32x64 9.0 / 7.7 (576); FP64 8x8x40 6.3 / 6.3, 32x32x64
+//     11.7 / 9.7 (576), 25x53x64 17.7 / 13.4 (1152).  Where FP64 z is not half filled, a
+//     second round of the 1024 waves that the chip holds costs the gain while k_zmul has
+//     its 64-byte tile (below 2048): 6 of 16x16x48 15.4 / 10.5 (960), but Heun steps of
+//     25x53x44 88.6 / 93.9 (1152) and 114x17x57 101.2 / 103.6 (1584), of 64x64x48 (2176)
+//     again 151 / 123.  The
+//     FP32 tile is 32 bytes of each z row, which pays while the spectra stay in the
+//     256 MB cache: 128x128x64 47 / 42 (105 MB), 200x200x64 171 / 245 (203 MB)
 template <typename T, int MZ>
 static bool zcol_wins(const Geom &g)
 {
     const long long cols = (long long)hx_blocked(g.hx) * g.nb * g.my;
     const long long waves = cols * (MZ / 8) / 64;
-    if (sizeof(T) == 8) return MZ == 128 ? waves >= 512 : 2 * g.nz == MZ && waves >= 2048;
-    if (MZ == 128) return 3 * cols * g.nz * (long long)sizeof(cpx<T>) <= 128LL << 20;
+    if (sizeof(T) == 8 && MZ == 128)
+        return waves >= 512 && (2 * g.nz == MZ || waves <= 1024 || waves >= 2048);
+    if (sizeof(T) == 8) return 2 * g.nz == MZ && waves >= 2048;
+    if (MZ == 128)
+        return (waves <= 256 || waves >= 512) &&
+               3 * cols * g.nz * (long long)sizeof(cpx<T>) <= 128LL << 20;
     return waves >= 3200;
 }
 
