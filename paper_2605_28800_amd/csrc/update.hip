@@ -635,8 +635,13 @@ static int update_threads(const Geom &g, int yt, int tpl)
 // groups at 8).  Long rows fill a group with few of
 // them: at most 4 FP32 rows of 192 or 256 points (16 boxes of 96x96x8 206 / 217 /
 // 210), 8 of 384 (190x180x20 216 / 207 / -), 8 FP64 rows from 96 points on (8 boxes
-// of 48x40x12 120 / 109 / 122), 2 from 512.  Small grids keep 8 short or 4 longer
-// rows.
+// of 48x40x12 120 / 109 / 122; one of 64x64x64 127 / 112 / -; at 192 points 8 of 96x96x8
+// 216.5 / 215.6 / -, from 256 on the 512 threads hold 4), 2 from 512.  FP32 rows of 256
+// points: one 128x128x32 box 111.3 / 112.2 / -, 256x256x32 film 173 / 179 / -, 4 of
+// 128x64x16 101.8 / 102.8 / -.  16 FP32 rows only where the last group is filled well
+// enough, at most 15 % more rows in all than with 8: 38 of 58x17x4 69.4 / 70.1 / 73.8 (32
+// rows for 17), 20 of 60x24x12 87 / 79.4 / 81.3, but 8 of 32x50x16 (64 for 50) 86 / 79 / 78.
+// Small grids keep 8 short or 4 longer rows.
 template <typename T, int M>
 static int rows_for(const Geom &g, bool step)
 {
@@ -651,8 +656,10 @@ static int rows_for(const Geom &g, bool step)
     for (int yt = 2; yt <= ymax && yt <= (ny_even > 2 ? ny_even : 2); yt *= 2) {
         if (update_threads(g, yt, HalfLine<M / 2>::TPL) > maxthr) break;
         if (yt > 2 && update_lds<T, M>(g, yt) > 65536) break;
-        if (step && yt > ymin &&
-            (long long)((g.ny + yt - 1) / yt) * g.nz * g.nb < (sizeof(T) == 4 ? 256 : 400))
+        const int groups = (g.ny + yt - 1) / yt;
+        if (step && yt > ymin && (long long)groups * g.nz * g.nb < (sizeof(T) == 4 ? 256 : 400))
+            break;
+        if (step && sizeof(T) == 4 && yt == 16 && 100 * 16 * groups > 115 * 8 * ((g.ny + 7) / 8))
             break;
         best = yt;
     }
