@@ -407,8 +407,9 @@ const void *tw(const tdgl_ctx *c) { return c->prec == PREC_F32 ? c->twf : c->twd
 //     multiples of the 8 XCDs, each of which then reads one instance's planes, from
 //     100 on: 8 of 16x16x32 (136) 37.2 / 42.7, 49.3 / 62.5; 7 of them (119) 43.5 / 42.1
 //   the longest z transforms, of which the passes are dear: 8 of 8x8x60 (960 points, 72
-//     groups) 34.0 / 39.6, 47.9 / 52.3; the shortest, in boxes with wide planes:
-//     120x120x3 (768, 129) 42.2 / 45.3, 53.3 / 59.8
+//     groups) 34.0 / 39.6, 47.9 / 52.3; the shortest, in boxes with wide planes: 4 of
+//     24x100x4 (1024, 100) 40.9 / 43.9, 49.3 / 57.8, 120x120x3 (768, 129) 42.2 / 45.3,
+//     53.3 / 59.8, but 60x128x3 (768, 65) 37.1 / 35.0, 45.3 / 44.5
 //   more groups than CUs: 8 of 32x32x9 FP32 (576 points, 264) 57.4 / 45.7; FP64, where
 //     the passes take longer, up to a few more: 75.0 / 76.7, 8 of 30x30x10 75.8 / 81.8,
 //     but 4 of 60x60x5 (260, no multiple of 8) 83.8 / 71.8
@@ -423,7 +424,7 @@ bool plane_wins(int prec, const Geom &g)
     const bool more = prec == PREC_F64 && xcd && (g.mz == 16 || g.mz == 32);
     if (points > 1024 || groups > (more ? 288 : 256)) return false;
     if (g.mz >= 128) return groups >= (xcd ? 64 : 100);
-    if (g.mz == 8) return groups >= 128;
+    if (g.mz == 8) return groups >= 90;
     return groups >= (xcd ? 100 : (prec == PREC_F32 ? 180 : 150));
 }
 
