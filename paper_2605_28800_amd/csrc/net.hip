@@ -61,31 +61,28 @@ __device__ inline long long gather_index(const Pos &p, int dz, int dy, int dx, i
 }
 
 // ----------------------------------------------------------------- conv
-// element index of the 8 packed weights of rows 16 m + col, tap t, channels
-// ci .. ci + 7 (ci a multiple of 8); co16: 16-row blocks
-__device__ __forceinline__ size_t packed_at(int co16, int m, int col, int t, int ci) {
-  const int c = ci >> 4, kq = 2 * (t & 1) + ((ci >> 3) & 1);
-  return (((size_t)c * 14 + (t >> 1)) * co16 + m) * 512 + (kq * 16 + col) * 8;
-}
-
 // Small grids.  One work-group: 4 waves x 16 * NB output positions, 16 * MB
 // output channels (blockIdx.y selects the channel block).  K = 27 * cin_p runs
 // in steps of 32: each lane gathers 8 consecutive input channels of one tap
 // for each of its NB position columns, and 8 consecutive weights per 16-row
 // block; the operands of step k + 1 are loaded while step k's MFMAs run.
-template <int MB, int NB>
-__device__ __forceinline__ void conv_operands(const ConvArgs &a, int co_blk, int col, int kp,
+// wl: the weights of this lane's row (16 m + col of block m = 0); plain rows kp apart,
+// packed ones co16 blocks of 16 rows a step
+template <int MB, int NB, bool PACKED>
+__device__ __forceinline__ void conv_operands(const ConvArgs &a, const bf16_t *wl, int kp, int co16,
                                               int lc, int k0, int kq, const Pos *p,
                                               const bool *inb, bf16x8 *av, bf16x8 *bv) {
   const int k = k0 + 8 * kq;
   const bool kv = k < kp;
   const int t = k >> lc, ci = k & (a.cin_p - 1);
   const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-  for (int mb = 0; mb < MB; ++mb) {
-    const size_t o = a.packed ? packed_at(a.cout_p >> 4, (co_blk >> 4) + mb, col, t, ci)
-                              : (size_t)(co_blk + mb * 16 + col) * kp + k;
-    av[mb] = kv ? load8(a.w + o) : zero8();
+  const bf16_t *w = wl + k;
+  int block = 16 * kp;
+  if (PACKED) {
+    w = wl + (size_t)((ci >> 4) * 14 + (t >> 1)) * co16 * 512 + (2 * (t & 1) + (ci >> 3 & 1)) * 128;
+    block = 512;
   }
+  for (int mb = 0; mb < MB; ++mb) av[mb] = kv ? load8(w + (size_t)mb * block) : zero8();
   for (int j = 0; j < NB; ++j) {
     long long src = -1;
     if (kv && inb[j]) src = gather_index(p[j], dz, dy, dx, a.lx, a.ly, a.lz, a.in_up2);
@@ -150,7 +147,7 @@ __device__ __forceinline__ void conv_store(const ConvArgs &a, const Pos &p, long
   }
 }
 
-template <int MB, int NB, int EPI>
+template <int MB, int NB, int EPI, bool PACKED>
 __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kq = lane >> 4, col = lane & 15;
@@ -173,11 +170,15 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
   for (int mb = 0; mb < MB; ++mb)
     for (int j = 0; j < NB; ++j) acc[mb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+  const int co16 = a.cout_p >> 4;
+  const bf16_t *wl = PACKED ? a.w + (size_t)(co_blk >> 4) * 512 + col * 8
+                            : a.w + (size_t)(co_blk + col) * kp;
   bf16x8 av[MB], bv[NB];
-  conv_operands<MB, NB>(a, co_blk, col, kp, lc, 0, kq, p, inb, av, bv);
+  conv_operands<MB, NB, PACKED>(a, wl, kp, co16, lc, 0, kq, p, inb, av, bv);
   for (int k0 = 0; k0 < kp; k0 += 32) {
     bf16x8 an[MB], bn[NB];
-    if (k0 + 32 < kp) conv_operands<MB, NB>(a, co_blk, col, kp, lc, k0 + 32, kq, p, inb, an, bn);
+    if (k0 + 32 < kp)
+      conv_operands<MB, NB, PACKED>(a, wl, kp, co16, lc, k0 + 32, kq, p, inb, an, bn);
     for (int mb = 0; mb < MB; ++mb)
       for (int j = 0; j < NB; ++j)
         acc[mb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mb], bv[j], acc[mb][j], 0, 0, 0);
@@ -409,6 +410,17 @@ static hipError_t conv_pick(const ConvArgs &a, long long npos, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// the kernel for small grids
+template <int MB, int NB, int EPI>
+static hipError_t conv_small(const ConvArgs &a, long long npos, hipStream_t s) {
+  const long long blocks = (npos + 64 * NB - 1) / (64 * NB);
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks, a.cout_p / (16 * MB), 1);
+  if (a.packed) hipLaunchKernelGGL((k_conv<MB, NB, EPI, true>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_conv<MB, NB, EPI, false>), grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 // positions per wave: 16 * NB with MB * NB = 16 accumulator tiles (NB >= 2)
 template <int EPI>
 static hipError_t conv_mb(const ConvArgs &a, long long npos, hipStream_t s) {
@@ -417,18 +429,13 @@ static hipError_t conv_mb(const ConvArgs &a, long long npos, hipStream_t s) {
       ((6LL * (a.cin_p / 8)) << (a.lx + a.ly)) < (1LL << 31))
     return conv_pick<EPI>(a, npos, s);
   const int mb = a.cout_p / 16 >= 8 ? 8 : a.cout_p / 16;
-  const int nbk = mb >= 8 ? 2 : 16 / mb > 8 ? 8 : 16 / mb;
-  const long long blocks = (npos + 64 * nbk - 1) / (64 * nbk);
-  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  dim3 grid((unsigned)blocks, a.cout_p / (16 * mb), 1);
   switch (mb) {
-    case 1: hipLaunchKernelGGL((k_conv<1, 8, EPI>), grid, dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_conv<2, 8, EPI>), grid, dim3(256), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((k_conv<4, 4, EPI>), grid, dim3(256), 0, s, a); break;
-    case 8: hipLaunchKernelGGL((k_conv<8, 2, EPI>), grid, dim3(256), 0, s, a); break;
+    case 1: return conv_small<1, 8, EPI>(a, npos, s);
+    case 2: return conv_small<2, 8, EPI>(a, npos, s);
+    case 4: return conv_small<4, 4, EPI>(a, npos, s);
+    case 8: return conv_small<8, 2, EPI>(a, npos, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 static bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
