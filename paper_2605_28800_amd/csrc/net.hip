@@ -278,15 +278,19 @@ void k_conv_tile(ConvArgs a) {
   };
   const int kp = 27 * a.cin_p, co16 = a.cout_p >> 4;
   const bf16_t *wl = PACKED ? a.w + (size_t)(co_blk >> 4) * 512 + lane * 8
-                            : a.w + (size_t)(co_blk + col) * kp + 8 * (kq & 1);
+                            : a.w + (size_t)co_blk * kp;
+  // plain weights: this lane's row, tap (of a step's two) and channels, behind an
+  // offset that is the same for all lanes; as one address per lane and load, the
+  // compiler kept them all in registers and spilled 196 bytes a lane (<4, 4>)
+  const unsigned wo = (unsigned)(col * kp + 8 * (kq & 1) + (kq >> 1) * a.cin_p);
   auto weights = [&](int c, int s, bf16x8 *av) {   // step s of chunk c
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       if (PACKED) {
         av[mb] = load8(wl + ((size_t)(c * 14 + s) * co16 + mb) * 512);
       } else {
-        const int t = 2 * s + (kq >> 1);
-        av[mb] = t < 27 ? load8(wl + (size_t)mb * 16 * kp + t * a.cin_p + 16 * c) : zero8();
+        const bf16_t *base = wl + (size_t)mb * 16 * kp + (2 * s * a.cin_p + 16 * c);
+        av[mb] = s < 13 || kq < 2 ? load8(base + wo) : zero8();
       }
     }
   };
