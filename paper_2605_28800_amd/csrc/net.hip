@@ -1044,15 +1044,22 @@ hipError_t launch_sum_partials(const double *partials, int n, double *out, hipSt
 }
 
 // flat gradient of one layer (public order: W [cout][27][cin], then b [cout]):
-// 32 entries per work-group, 8 threads each taking every eighth split, so that
+// 256 / SL entries per work-group, SL threads each taking every SL-th split, so that
 // the hundreds of splits of a small layer are not one thread's chain of loads
-// (19 us a layer before, 11 now, 8 films of 64x64x16, width 32)
+// (SL = 8: 19 us a layer with one thread an entry, 11 with eight, 8 films of
+// 64x64x16, width 32), while the few splits of a wide layer on a small grid do not
+// leave seven of eight threads idle (SL = 1: 4 splits of 256 x 27 x 256, with the
+// weight gradient 40 us against 59).
+constexpr int REDUCE_SLICES = 64;      // splits from which an entry has eight threads
+
+template <int SL>
 __global__ __launch_bounds__(256) void k_reduce_grad(const float *part, const float *bpart,
                                                      int splits, int cin, int cout, int cin_p,
                                                      int cout_p, float *grad) {
-  __shared__ float red[8][32];
-  const int e = threadIdx.x & 31, sg = threadIdx.x >> 5;
-  const long long i = (long long)blockIdx.x * 32 + e;
+  constexpr int E = 256 / SL;
+  __shared__ float red[SL][E];
+  const int e = threadIdx.x % E, sg = threadIdx.x / E;
+  const long long i = (long long)blockIdx.x * E + e;
   const long long nw = (long long)cout * 27 * cin;
   float s = 0.f;
   if (i < nw + cout) {
@@ -1067,22 +1074,26 @@ __global__ __launch_bounds__(256) void k_reduce_grad(const float *part, const fl
       stride = (size_t)cout_p * kp;
     }
 #pragma unroll 8
-    for (int sp = sg; sp < splits; sp += 8) s += src[(size_t)sp * stride];
+    for (int sp = sg; sp < splits; sp += SL) s += src[(size_t)sp * stride];
   }
-  red[sg][e] = s;
-  __syncthreads();
-  if (sg == 0 && i < nw + cout) {
-    for (int k = 1; k < 8; ++k) s += red[k][e];
-    grad[i] = s;
+  if constexpr (SL > 1) {
+    red[sg][e] = s;
+    __syncthreads();
+    if (sg != 0) return;
+    for (int k = 1; k < SL; ++k) s += red[k][e];
   }
+  if (i < nw + cout) grad[i] = s;
 }
 
 hipError_t launch_reduce_grad(const float *part, const float *bpart, int splits, int cin,
                               int cout, int cin_p, int cout_p, float *grad, hipStream_t s) {
   const long long n = (long long)cout * 27 * cin + cout;
-  hipLaunchKernelGGL(k_reduce_grad, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, s, part,
-                     bpart, splits, cin, cout, cin_p, cout_p, grad);
-  return hipGetLastError();
+  auto launch = [&](auto kernel, int entries) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + entries - 1) / entries)), dim3(256), 0, s, part,
+                       bpart, splits, cin, cout, cin_p, cout_p, grad);
+    return hipGetLastError();
+  };
+  return splits < REDUCE_SLICES ? launch(k_reduce_grad<1>, 256) : launch(k_reduce_grad<8>, 32);
 }
 
 // omb1 = 1 - beta1, omb2 = 1 - beta2 and the bias corrections c1, c2 come
