@@ -710,12 +710,21 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
 // 64x64x16, width 32: 440 us with 256 groups, 344 with 512, 398 with 768).
 constexpr long long WGRAD_GROUPS = 512;
 
-// channel blocks of a work-group of the tiled kernel: 28 accumulator tiles
-// per wave where the layer has the channels
+// tiles of 4 x 8 x 8 positions (fewer in z in a flatter grid)
+static long long wgrad_tiles(const WgradArgs &a) {
+  return ((long long)a.nb << (a.lx + a.ly + a.lz)) >> (6 + (a.lz < 2 ? a.lz : 2));
+}
+
+// Channel blocks of a work-group of the tiled kernel: 28 accumulator tiles per
+// wave where the layer has the channels and the grid the tiles; where that would
+// leave fewer than 256 groups, one per CU, each takes 16 x 16 channels: one sample
+// of 4x32x32, 32 to 64 channels, 14.4 -> 10.3 us (13.9 with k_wgrad), of 4x16x16,
+// 64 to 64, 14.0 -> 9.8 (10.8), 4 of 4x32x32, 32 to 64, 19.1 -> 16.0 (33.1).
 static void wgrad_blocks(const WgradArgs &a, int *A, int *B) {
   const int co16 = a.cout_p / 16, ci16 = a.cin_p / 16;
   *A = co16 >= 4 ? 4 : co16;
   *B = *A == 4 || ci16 == 1 ? 1 : 2;
+  if (wgrad_tiles(a) * (ci16 / *B) * (co16 / *A) < 256) *A = *B = 1;
 }
 
 void wgrad_plan(WgradArgs *a) {
@@ -726,7 +735,7 @@ void wgrad_plan(WgradArgs *a) {
   if (a->tiled) {
     int A, B;
     wgrad_blocks(*a, &A, &B);
-    const long long tiles = npos >> (6 + (a->lz < 2 ? a->lz : 2));
+    const long long tiles = wgrad_tiles(*a);
     const long long blocks = (long long)(a->cin_p / (16 * B)) * (a->cout_p / (16 * A));
     long long s = (WGRAD_GROUPS + blocks - 1) / blocks;
     if (s > tiles) s = tiles;
