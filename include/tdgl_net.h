@@ -137,7 +137,10 @@ tdgl_status tdgl_nn_conv3(int epi, const void *in, int in_up2, const void *w, co
                           void *out2, const void *aux, float *P, const float *thick,
                           void *hip_stream);
 
-/* Workspace bytes of tdgl_nn_conv3_wgrad for these sizes. */
+/* Workspace bytes of tdgl_nn_conv3_wgrad for these sizes: partial sums, as many as
+ * are fastest.  Layers of grids from 8 x 8 in y and x on also take fewer, at a
+ * loss of speed, down to one for every 256 positions or
+ * ceil(1024 / ceil(27 cin_p / 64)), whichever is less. */
 tdgl_status tdgl_nn_wgrad_workspace(int nb, int lx, int ly, int lz, int cin_p, int cout_p,
                                     size_t *bytes);
 

@@ -727,26 +727,12 @@ static void wgrad_blocks(const WgradArgs &a, int *A, int *B) {
   if (wgrad_tiles(a) * (ci16 / *B) * (co16 / *A) < 256) *A = *B = 1;
 }
 
-void wgrad_plan(WgradArgs *a) {
+// the splits of k_wgrad: about 1024 work-groups, at least 256 positions each
+static void plan_small(WgradArgs *a) {
   const long long npos = (long long)a->nb << (a->lx + a->ly + a->lz);
-  const int kp = 27 * a->cin_p, cmax = a->cin_p > a->cout_p ? a->cin_p : a->cout_p;
-  // (the offsets within a tile's planes fit 31 bits)
-  a->tiled = a->lx >= 3 && a->ly >= 3 && ((6LL * (cmax / 8)) << (a->lx + a->ly)) < (1LL << 31);
-  if (a->tiled) {
-    int A, B;
-    wgrad_blocks(*a, &A, &B);
-    const long long tiles = wgrad_tiles(*a);
-    const long long blocks = (long long)(a->cin_p / (16 * B)) * (a->cout_p / (16 * A));
-    long long s = (WGRAD_GROUPS + blocks - 1) / blocks;
-    if (s > tiles) s = tiles;
-    a->max_splits = (int)s;
-    a->chunk = (int)((tiles + s - 1) / s);
-    a->splits = (int)((tiles + a->chunk - 1) / a->chunk);
-    return;
-  }
-  const long long ktiles = (kp + 63) / 64;
-  long long s = (1024 + ktiles - 1) / ktiles;           // aim at ~1024 work-groups
-  const long long smax = (npos + 255) / 256;            // at least 256 positions each
+  const long long ktiles = (27LL * a->cin_p + 63) / 64;
+  long long s = (1024 + ktiles - 1) / ktiles;
+  const long long smax = (npos + 255) / 256;
   if (s > smax) s = smax;
   if (s < 1) s = 1;
   a->max_splits = (int)s;
@@ -755,6 +741,32 @@ void wgrad_plan(WgradArgs *a) {
   s = (npos + c - 1) / c;
   a->splits = (int)s;
   a->chunk = (int)c;
+}
+
+void wgrad_plan(WgradArgs *a, int most) {
+  const int cmax = a->cin_p > a->cout_p ? a->cin_p : a->cout_p;
+  // (the offsets within a tile's planes fit 31 bits)
+  a->tiled = a->lx >= 3 && a->ly >= 3 && ((6LL * (cmax / 8)) << (a->lx + a->ly)) < (1LL << 31);
+  if (!a->tiled) {
+    plan_small(a);
+    return;
+  }
+  int A, B;
+  wgrad_blocks(*a, &A, &B);
+  const long long tiles = wgrad_tiles(*a);
+  const long long blocks = (long long)(a->cin_p / (16 * B)) * (a->cout_p / (16 * A));
+  long long s = (WGRAD_GROUPS + blocks - 1) / blocks;
+  if (s > tiles) s = tiles;
+  if (most > 0 && s > most) s = most;
+  a->max_splits = (int)s;
+  a->chunk = (int)((tiles + s - 1) / s);
+  a->splits = (int)((tiles + a->chunk - 1) / a->chunk);
+}
+
+int wgrad_least_splits(const WgradArgs &a) {
+  WgradArgs u = a;
+  plan_small(&u);
+  return u.splits < a.splits ? u.splits : a.splits;
 }
 
 hipError_t launch_wgrad(const WgradArgs &a, hipStream_t s) {

@@ -598,7 +598,7 @@ tdgl_status tdgl_nn_conv3_wgrad(const void *g, const void *in, int in_up2, int n
                                 float *grad, void *hip_stream) {
   size_t need = 0;
   if (tdgl_nn_wgrad_workspace(nb, lx, ly, lz, cin_p, cout_p, &need) != TDGL_OK || !g || !in ||
-      !workspace || !grad || ws_bytes < need)
+      !workspace || !grad)
     return TDGL_E_ARG;
   WgradArgs a{};
   a.g = static_cast<const bf16_t *>(g);
@@ -611,6 +611,11 @@ tdgl_status tdgl_nn_conv3_wgrad(const void *g, const void *in, int in_up2, int n
   a.cin_p = cin_p;
   a.cout_p = cout_p;
   wgrad_plan(&a);
+  const size_t split = (size_t)cout_p * (27 * (size_t)cin_p + 1) * sizeof(float);
+  if (ws_bytes < need) {           // fewer splits, down to those of the kernel of small grids
+    if (ws_bytes < wgrad_least_splits(a) * split) return TDGL_E_ARG;
+    wgrad_plan(&a, (int)(ws_bytes / split));
+  }
   a.part = static_cast<float *>(workspace);
   a.bpart = a.part + (size_t)a.splits * cout_p * 27 * cin_p;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);

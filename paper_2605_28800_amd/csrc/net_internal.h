@@ -65,7 +65,11 @@ struct WgradArgs {
 
 hipError_t launch_conv(int epi, const ConvArgs &a, hipStream_t s);
 hipError_t launch_wgrad(const WgradArgs &a, hipStream_t s);
-void wgrad_plan(WgradArgs *a);    // from the grid and the channels
+// from the grid and the channels; most: at most so many splits (0: as many as pay),
+// for a tiled plan no fewer than wgrad_least_splits, which is what the kernel of small
+// grids would use
+void wgrad_plan(WgradArgs *a, int most = 0);
+int wgrad_least_splits(const WgradArgs &planned);
 
 // elementwise parts
 // ops: per-sample in-plane symmetry op (bits: 1 mirror x, 2 mirror y, 4 swap

@@ -1,6 +1,9 @@
 """The tiled weight gradient at each of its channel blocks, on both sides of the
-256 groups below which it takes blocks of 16 x 16 channels: bit for bit against
-the oracle on inputs whose products and sums are exact in FP32."""
+256 groups below which it takes blocks of 16 x 16 channels, and in a workspace of
+fewer splits than it asks for: bit for bit against the oracle on inputs whose
+products and sums are exact in FP32."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -8,6 +11,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+import paper_2605_28800_amd as T  # noqa: E402
 from oracle import nn_oracle as N  # noqa: E402
 from tests.gpu_helpers import announce  # noqa: E402
 from tests.test_gpu_net import _rng, channels_last, dev_bf16  # noqa: E402
@@ -55,3 +59,33 @@ def test_channel_blocks_bit_exact(case):
                              nb, lx, ly, lz, cin, cout, in_up2=up2)
     torch.cuda.synchronize()
     check(grad, cin, cout, want)
+
+
+@pytest.mark.parametrize("case", [(32, 64, 32, (3, 3, 4), 0), (16, 16, 256, (0, 3, 3), 0),
+                                  (64, 64, 4, (2, 4, 4), 0), (16, 32, 64, (1, 3, 5), 1)], ids=ident)
+def test_smaller_workspace_is_taken_with_fewer_splits(case):
+    cin, cout, nb, (lz, ly, lx), up2 = case
+    announce("wgrad workspace %s" % (case,))
+    x, g, want = data(case)
+    dg, dx = dev_bf16(channels_last(g, cout)), dev_bf16(channels_last(x, cin))
+    full = ctypes.c_size_t()
+    assert T.lib().tdgl_nn_wgrad_workspace(nb, lx, ly, lz, cin, cout, ctypes.byref(full)) == T.TDGL_OK
+    split = 4 * cout * (27 * cin + 1)
+    npos = nb << (lz + ly + lx)
+    small = min(-(-1024 // -(-27 * cin // 64)), -(-npos // 256))     # splits of the other kernel
+    chunk = -(-(-(-npos // small)) // 128) * 128
+    least = min(-(-npos // chunk), full.value // split)
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    for splits in sorted({least, (least + full.value // split) // 2, full.value // split}):
+        guard = 1024
+        ws = torch.full((splits * split // 4 + guard,), 7.0, dtype=torch.float32, device="cuda")
+        grad = torch.empty(cout * 27 * cin + cout, dtype=torch.float32, device="cuda")
+        call = lambda nbytes: T.lib().tdgl_nn_conv3_wgrad(
+            ptr(dg), ptr(dx), up2, nb, lx, ly, lz, cin, cout, ptr(ws), ctypes.c_size_t(nbytes),
+            ptr(grad), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert call(splits * split) == T.TDGL_OK
+        torch.cuda.synchronize()
+        check(grad, cin, cout, want)
+        assert (ws[-guard:] == 7.0).all()
+        if splits == least:
+            assert call(splits * split - 1) == T.TDGL_E_ARG
