@@ -117,6 +117,7 @@ struct tdgl_ctx {
     bool hist_own = false, rk_own = false, x_own = false;
     double rk_h = 0.0, rk_tau = 0.0, rk_atol = 1e-8, rk_rtol = 1e-6;
     long long rk_rejected = 0;
+    int rk_plain = 0;             // RK45 attempts launched plainly since the graphs were dropped
     int hist_count = 0;           // valid history entries (0..2)
     int hist_pos = 0;             // buffer of the newest entry
     size_t lds_max = 65536;      // dynamic LDS one work-group may use on this device
@@ -557,6 +558,7 @@ void drop_graphs(tdgl_ctx *c)
     for (auto &e : c->graphs)
         if (e.exec) (void)hipGraphExecDestroy(e.exec);
     c->graphs.clear();
+    c->rk_plain = 0;
 }
 
 bool elec_on(const tdgl_ctx *c) { return (c->terms & TDGL_ELEC) != 0; }
@@ -1406,10 +1408,15 @@ tdgl_status extra_buffer(tdgl_ctx *c, int scheme, size_t bytes, void **out, bool
                 c->ws_bytes, bytes, L.total);
 }
 
+size_t state_bytes(const tdgl_ctx *c)
+{
+    return (size_t)3 * c->g.nx * c->g.ny * c->g.nz * c->g.nb * c->esz;
+}
+
 // One RK45 attempt from P_n = P[cur], then the decision on it (RkState)
 hipError_t enq_rk_attempt(tdgl_ctx *c, hipStream_t s)
 {
-    const size_t pbytes = (size_t)3 * c->g.nx * c->g.ny * c->g.nz * c->g.nb * c->esz;
+    const size_t pbytes = state_bytes(c);
     const bool el = elec_on(c);
     void *Pn = c->P[c->cur], *W0 = c->P[1 - c->cur];
     void *Q = c->rkbuf;
@@ -1454,16 +1461,19 @@ hipError_t enq_rk_attempt(tdgl_ctx *c, hipStream_t s)
 }
 
 // nsteps accepted RK45 steps.  The attempts that are still needed are enqueued
-// together, each a graph of its own (the step size, the decision and the
-// tolerances live on the device), and the host looks once behind them: without
-// rejections one synchronisation per call.  Launched eagerly with a look after
-// every attempt, 6 steps of a 48x40x12 FP64 box took 1.82 ms, now 1.64; of
-// a 16x16x8 box 1.13, now 0.97.
+// together (the step size, the decision and the tolerances live on the device),
+// and the host looks once behind them: without rejections one synchronisation per
+// call.  An attempt is a graph once a context has run RK_PLAIN of them: its capture
+// costs as much as four attempts gain, and 2 ms for the first in a process, which
+// a short run does not earn back.
+// Launched eagerly with a look after every attempt, 6 steps of a 48x40x12 FP64 box
+// took 1.82 ms, now 1.64; of a 16x16x8 box 1.13, now 0.97.
+constexpr int RK_PLAIN = 8;
+
 tdgl_status rk45_steps(tdgl_ctx *c, long long nsteps)
 {
     if (!c->rkbuf) {
-        const size_t pbytes = (size_t)3 * c->g.nx * c->g.ny * c->g.nz * c->g.nb * c->esz;
-        tdgl_status st = extra_buffer(c, TDGL_RK45, 8 * pbytes, &c->rkbuf, &c->rk_own);
+        tdgl_status st = extra_buffer(c, TDGL_RK45, 8 * state_bytes(c), &c->rkbuf, &c->rk_own);
         if (st != TDGL_OK) return st;
     }
     const bool el = elec_on(c);
@@ -1478,13 +1488,14 @@ tdgl_status rk45_steps(tdgl_ctx *c, long long nsteps)
         RkState r{};
         while (r.accepted < want && r.fail == 0) {
             for (long long i = r.accepted; i < want; ++i) {
-                if (c->graph_chunk > 0) {
+                if (c->graph_chunk > 0 && c->rk_plain >= RK_PLAIN) {
                     hipGraphExec_t exec = nullptr;
                     tdgl_status st = get_graph(c, 1, &exec);
                     if (st != TDGL_OK) return st;
                     HIP_TRY(c, hipGraphLaunch(exec, c->stream));
                 } else {
                     HIP_TRY(c, enq_rk_attempt(c, c->stream));
+                    if (c->rk_plain < RK_PLAIN) ++c->rk_plain;
                 }
             }
             HIP_TRY(c, hipMemcpyAsync(&r, c->rk, sizeof r, hipMemcpyDeviceToHost, c->stream));
