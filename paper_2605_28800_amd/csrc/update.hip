@@ -644,7 +644,13 @@ static int update_threads(const Geom &g, int yt, int tpl)
 // points: one 128x128x32 box 111.3 / 112.2 / -, 256x256x32 film 173 / 179 / -, 4 of
 // 128x64x16 101.8 / 102.8 / -.  16 FP32 rows only where the last group is filled well
 // enough, at most 15 % more rows in all than with 8: 38 of 58x17x4 69.4 / 70.1 / 73.8 (32
-// rows for 17), 20 of 60x24x12 87 / 79.4 / 81.3, but 8 of 32x50x16 (64 for 50) 86 / 79 / 78.
+// rows for 17), 20 of 60x24x12 87 / 79.4 / 81.3, but 8 of 32x50x16 (64 for 50) 86 / 79 / 78;
+// and where the last round of groups fills the CUs (unless they have no more threads
+// than groups of 8): films of 128x64x8, 8 of them (256
+// groups at 16) 56.6 / 55.0 / 48.8, 9 (288) 85.5 / 86.3 / 89.6; a 128x128x37 film (296) - /
+// 87.0 / 89.4.  The same for 8 long FP64 rows beyond two rounds: 6 films of 128x64x10
+// (480 groups at 8) 102 / 99 / -, 7 (560) 119.3 / 121.7 / -, 19 of 128x128x2 (608) 148.6 /
+// 151.1 / -.
 // Small grids keep 8 short or 4 longer rows.
 template <typename T, int M>
 static int rows_for(const Geom &g, bool step)
@@ -663,7 +669,18 @@ static int rows_for(const Geom &g, bool step)
         const int groups = (g.ny + yt - 1) / yt;
         if (step && yt > ymin && (long long)groups * g.nz * g.nb < (sizeof(T) == 4 ? 256 : 400))
             break;
-        if (step && sizeof(T) == 4 && yt == 16 && 100 * 16 * groups > 115 * 8 * ((g.ny + 7) / 8))
+        // groups that the chip holds at a time, by their registers 1024 FP32 or 512 FP64
+        // threads a CU, and the rounds they take
+        const int nthr = update_threads(g, yt, HalfLine<M / 2>::TPL);
+        const long long total = (long long)groups * g.nz * g.nb;
+        const long long held = 256LL * (nthr < maxthr ? maxthr / nthr : 1);
+        const long long rounds = (total + held - 1) / held;
+        if (step && sizeof(T) == 4 && yt == 16 &&
+            (100 * 16 * groups > 115 * 8 * ((g.ny + 7) / 8) ||
+             (nthr > update_threads(g, 8, HalfLine<M / 2>::TPL) && 10 * total < 9 * held * rounds)))
+            break;
+        if (step && sizeof(T) == 8 && yt == 8 && M >= 96 && rounds > 2 &&
+            100 * total < 83 * held * rounds)
             break;
         best = yt;
     }
