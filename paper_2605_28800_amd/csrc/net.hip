@@ -395,23 +395,29 @@ static hipError_t conv_tile(const ConvArgs &a, hipStream_t s) {
 // them, and in plain and packed weights.
 constexpr long long TILE_GROUPS = 512;
 
-template <int EPI>
-static hipError_t conv_pick(const ConvArgs &a, long long npos, hipStream_t s) {
+// the tile of a convolution: channel blocks and rows per wave; {0, 0}: k_conv
+struct ConvTile {
+  int mb, nr;
+};
+
+static ConvTile conv_tile_of(const ConvArgs &a, bool to_P) {
+  // (the input offsets of a halo fit 31 bits)
+  if (a.lx < 4 || a.ly < 1 || a.lz < 2 || ((6LL * (a.cin_p / 8)) << (a.lx + a.ly)) >= (1LL << 31))
+    return {0, 0};
+  const long long npos = (long long)a.nb << (a.lx + a.ly + a.lz);
   const int co16 = a.cout_p / 16, Y = 1 << a.ly;
   auto fits = [&](int mb, int nr) {
     return mb <= co16 && Y >= nr && npos / (64 * nr) * (co16 / mb) >= TILE_GROUPS;
   };
-  if (EPI == EPI_P || co16 == 1) {
-    if (fits(1, 8)) return conv_tile<1, 8, EPI>(a, s);
-    return conv_tile<1, 2, EPI>(a, s);
-  }
-  if constexpr (EPI != EPI_P) {
-    if (co16 == 2 && fits(2, 8)) return conv_tile<2, 8, EPI>(a, s);
-    if (fits(4, 4)) return conv_tile<4, 4, EPI>(a, s);
-    if (fits(2, 4)) return conv_tile<2, 4, EPI>(a, s);
-    return conv_tile<2, 2, EPI>(a, s);
-  }
-  return hipErrorInvalidValue;
+  if (to_P || co16 == 1) return fits(1, 8) ? ConvTile{1, 8} : ConvTile{1, 2};
+  if (co16 == 2 && fits(2, 8)) return {2, 8};
+  if (fits(4, 4)) return {4, 4};
+  return fits(2, 4) ? ConvTile{2, 4} : ConvTile{2, 2};
+}
+
+int conv_tile_code(const ConvArgs &a) {
+  const ConvTile t = conv_tile_of(a, false);
+  return 16 * t.mb + t.nr;
 }
 
 // the kernel for small grids
@@ -428,10 +434,13 @@ static hipError_t conv_small(const ConvArgs &a, long long npos, hipStream_t s) {
 // positions per wave: 16 * NB with MB * NB = 16 accumulator tiles (NB >= 2)
 template <int EPI>
 static hipError_t conv_mb(const ConvArgs &a, long long npos, hipStream_t s) {
-  // (the input offsets of a halo fit 31 bits)
-  if (a.lx >= 4 && a.ly >= 1 && a.lz >= 2 &&
-      ((6LL * (a.cin_p / 8)) << (a.lx + a.ly)) < (1LL << 31))
-    return conv_pick<EPI>(a, npos, s);
+  const ConvTile t = conv_tile_of(a, EPI == EPI_P);
+  if (t.mb == 1) return t.nr == 8 ? conv_tile<1, 8, EPI>(a, s) : conv_tile<1, 2, EPI>(a, s);
+  if constexpr (EPI != EPI_P) {
+    if (t.mb == 2 && t.nr == 8) return conv_tile<2, 8, EPI>(a, s);
+    if (t.mb == 4) return conv_tile<4, 4, EPI>(a, s);
+    if (t.mb == 2) return t.nr == 4 ? conv_tile<2, 4, EPI>(a, s) : conv_tile<2, 2, EPI>(a, s);
+  }
   const int mb = a.cout_p / 16 >= 8 ? 8 : a.cout_p / 16;
   switch (mb) {
     case 1: return conv_small<1, 8, EPI>(a, npos, s);

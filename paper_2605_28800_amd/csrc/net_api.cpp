@@ -626,4 +626,45 @@ tdgl_status tdgl_nn_conv3_wgrad(const void *g, const void *in, int in_up2, int n
   return e == hipSuccess ? TDGL_OK : TDGL_E_HIP;
 }
 
+int tdgl_internal_conv_tile(int nb, int lx, int ly, int lz, int cin_p, int cout_p) {
+  ConvArgs a{};
+  a.nb = nb;
+  a.lx = lx;
+  a.ly = ly;
+  a.lz = lz;
+  a.cin_p = cin_p;
+  a.cout_p = cout_p;
+  return conv_tile_code(a);
+}
+
+int tdgl_internal_conv3_packed(int epi, const void *in, int in_up2, const float *W, int mirror,
+                               int cin, int cout, int nb, int lx, int ly, int lz, int cin_p,
+                               int cout_p, void *out, void *out2, const void *aux, void *w,
+                               void *wt, float *bias, void *hip_stream) {
+  if (!W || !w || !wt || !bias || cin < 1 || cout < 1 || cin > cin_p || cout > cout_p ||
+      !pow2(cin_p) || cin_p < 16 || !pow2(cout_p) || cout_p < 16)
+    return TDGL_E_ARG;
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  hipError_t e = launch_cast_weights(W, cin, cout, cin_p, cout_p, static_cast<bf16_t *>(w),
+                                     static_cast<bf16_t *>(wt), bias, s);
+  ConvArgs a{};
+  a.in = static_cast<const bf16_t *>(in);
+  a.w = static_cast<const bf16_t *>(mirror ? wt : w);
+  a.packed = 1;
+  a.bias = mirror ? nullptr : bias;
+  a.out = static_cast<bf16_t *>(out);
+  a.out2 = static_cast<bf16_t *>(out2);
+  a.aux = static_cast<const bf16_t *>(aux);
+  a.in_up2 = in_up2 ? 1 : 0;
+  a.lx = lx;
+  a.ly = ly;
+  a.lz = lz;
+  a.nb = nb;
+  a.cin_p = mirror ? cout_p : cin_p;
+  a.cout_p = mirror ? cin_p : cout_p;
+  if (e == hipSuccess) e = launch_conv(epi, a, s);
+  if (e == hipErrorInvalidValue) return TDGL_E_ARG;
+  return e == hipSuccess ? TDGL_OK : TDGL_E_HIP;
+}
+
 }  // extern "C"

@@ -64,6 +64,7 @@ struct WgradArgs {
 };
 
 hipError_t launch_conv(int epi, const ConvArgs &a, hipStream_t s);
+int conv_tile_code(const ConvArgs &a);    // 16 * channel blocks + rows per wave; 0: small grids
 hipError_t launch_wgrad(const WgradArgs &a, hipStream_t s);
 // from the grid and the channels; most: at most so many splits (0: as many as pay),
 // for a tiled plan no fewer than wgrad_least_splits, which is what the kernel of small
@@ -96,3 +97,15 @@ hipError_t launch_cast_weights(const float *master, int cin, int cout, int cin_p
                                bf16_t *w, bf16_t *wt, float *bias, hipStream_t s);
 
 }  // namespace tdgl_nn
+
+// For tests.  The tile of a convolution of these sizes (conv_tile_code), and a
+// convolution with weights packed as the network packs them: W[cout][27][cin] and
+// bias[cout] behind it (device FP32), into w and wt of packed_size BF16 each and
+// bias of cout_p floats; mirror: the backward-data weights wt, from cout_p to cin_p
+// channels.
+extern "C" int tdgl_internal_conv_tile(int nb, int lx, int ly, int lz, int cin_p, int cout_p);
+extern "C" int tdgl_internal_conv3_packed(int epi, const void *in, int in_up2, const float *W,
+                                          int mirror, int cin, int cout, int nb, int lx, int ly,
+                                          int lz, int cin_p, int cout_p, void *out, void *out2,
+                                          const void *aux, void *w, void *wt, float *bias,
+                                          void *hip_stream);
