@@ -628,11 +628,16 @@ hipError_t prepare_slab(int prec, const Geom &g, size_t lds_max)
 //   16x16x8    FP32 23.3/26.7  23.7/24.3  40.7/44.9    FP64 25.8/29.5  27.6/27.3  65.8/66.5
 //   32x32x8    FP32 24.9/30.6  32.2/34.7  93.2/126     FP64 28.5/33.4  43.4/49.2  149/209
 //   32x32x16   FP32 28.0/31.6  42.9/56.0  158/172      FP64 34.7/37.7  65.7/75.5  288/319
+//   62x32x8    FP32 27.5/32.3  40.9/41.9  152/148      FP64 34.3/36.3  66.2/70.2  282/274
+//   15x32x32   FP32 30.0/31.0  43.4/58.7  175/187      FP64 35.9/37.9  64.3/73.1  305/344
+//   16x30x24   FP32 27.6/33.9  39.9/54.7  168/158      FP64 34.0/39.8  62.3/83.0  289/305
 // Wider slabs (w, the values of one y's spectra) wait longer than the launches
 // cost, sooner where few rows of y share the tensor pass: my = 32 at w = 1584,
 // 30x16x8, FP64 27.9/30.6 33.9/31.7 89.2/99.1, and at 3120 47.5/37.3 for 8 of
 // 60x16x8.  Thin boxes have cheap planes (nz my points) and a slab that is half
-// padding: 30x30x2 FP32 22.6/24.2 25.3/23.7 62.0/43.4; 16x32x20 (mz = 64) FP64
+// padding: 30x30x2 FP32 22.6/24.2 25.3/23.7 62.0/43.4; 64 of 32x8x3 FP64 40.4/38.3,
+// 256 FP32 60.6/49.3 (but 32x3x3 20.1/23.2 21.8/25.4 for 1 and 64, 16x8x3 37.3/35.7 only
+// for 256); 16x32x20 (mz = 64) FP64
 // 33.5/38.2 -/- 436/414 (100 of them).  Periodic films have no padding in x and
 // y to leave out: 32x32x8 FP32 24.1/27.4 -/- 72.3/57.4.  Lengths 3 * 2^a hold
 // 12 points a thread: 40x40x10, 8 of them, 0.82 of the three passes' speed.
@@ -645,7 +650,8 @@ bool slab_fits(const Geom &g)
     if (g.px || g.py || g.pz || g.mx < 16 || g.my > 64 || g.mz > 64) return false;
     if (!pow2(g.mx) || !pow2(g.my) || !pow2(g.mz) || 3 * g.nz < g.mz) return false;
     const int w = 3 * (g.mx / 2 + 1) * g.mz;       // mx <= 128 by the limits
-    return g.my <= 16 ? w <= 900 : g.nz >= 7 && w <= (g.my == 64 ? 3300 : 900);
+    if (g.my <= 16) return w <= (g.nz > 3 || g.my == 8 ? 900 : 500);
+    return g.nz >= 7 && w <= (g.my == 64 ? 3300 : 900);
 }
 
 }  // namespace tdgl

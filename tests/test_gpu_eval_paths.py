@@ -20,7 +20,8 @@ def eval_path(ctx):
 
 def _cfg(n, periodic=0, scheme="heun"):
     cfg = I.config("c1")
-    cfg.update(n=n, layers=[0] * n[2], periodic=(periodic, periodic, 0), scheme=scheme, mimg=1)
+    cfg.update(n=n, layers=[0] * n[2], scheme=scheme, mimg=1,
+               periodic=(int(periodic > 0), int(periodic > 0), int(periodic > 1)))
     return cfg
 
 
@@ -59,7 +60,8 @@ def test_rule(n, periodic, nb, p32, p64, prec):
         ctx.close()
 
 
-@pytest.mark.parametrize("n,used", BOXES)
+@pytest.mark.parametrize("n,used", BOXES + [((32, 8, 3), 0), ((32, 8, 4), 1), ((32, 4, 3), 1),
+                                           ((16, 8, 3), 1)])
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 def test_rule_of_the_two_kernels(n, used, prec):
     announce("two kernels of %s %s" % (n, prec))
@@ -77,11 +79,12 @@ def test_rule_of_the_two_kernels(n, used, prec):
 
 # every (my, mz) of planes of 513 to 1024 points: half-filled, ragged and
 # periodic y, z half-filled and not; open x of 24 points, which no two kernels take
+FULL = [(16, 64), (32, 32), (64, 16), (128, 8)]              # periodic in z as well
 PLANES = [(ny, nz, per) for nys, nzs in (((8, 7), (33, 64)), ((16, 13), (17, 32)),
                                         ((32, 31), (9, 16)), ((64, 50), (5, 8)),
                                         ((128, 101), (3, 4)))
           for ny, nz, per in [(nys[0], nzs[0], 0), (nys[1], nzs[1], 0), (2 * nys[0], nzs[0], 1),
-                              (2 * nys[0], nzs[1], 1)]]
+                              (2 * nys[0], nzs[1], 1)]] + [(ny, nz, 2) for ny, nz in FULL]
 
 
 @pytest.mark.parametrize("ny,nz,periodic", PLANES)
