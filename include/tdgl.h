@@ -264,8 +264,9 @@ tdgl_status tdgl_set_update_rows(tdgl_ctx *ctx, int rows);
  * 128 or 256; 0 restores the built-in choice: one wave per tile where there
  * are enough of them, otherwise 128, or 64 where that leaves fewer than 1024
  * work-groups).  A tuning knob: results do not depend on it.
- * tdgl_get_z_tile reports the tile set, or the row tile of the built-in
- * choice. */
+ * tdgl_get_z_tile reports the tile set, or the row tile that the built-in
+ * choice has for this grid (also where it takes one wave per tile: a value
+ * that tdgl_set_z_tile accepts). */
 tdgl_status tdgl_set_z_tile(tdgl_ctx *ctx, int row_bytes);
 tdgl_status tdgl_get_z_tile(const tdgl_ctx *ctx, int *row_bytes);
 
