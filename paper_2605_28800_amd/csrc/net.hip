@@ -104,8 +104,10 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // offset of channel co0 at the position.
 template <int EPI>
 __device__ __forceinline__ floatx4 conv_bias(const ConvArgs &a, int co0) {
-  if (EPI == EPI_ACT || EPI == EPI_ACT_SKIP || EPI == EPI_P)
-    return *reinterpret_cast<const floatx4 *>(a.bias + co0);
+  if (EPI == EPI_ACT || EPI == EPI_ACT_SKIP || EPI == EPI_P) {
+    typedef floatx4 floatx4_a4 __attribute__((aligned(4)));   // a caller's bias is an array of floats
+    return *reinterpret_cast<const floatx4_a4 *>(a.bias + co0);
+  }
   return floatx4{0.f, 0.f, 0.f, 0.f};
 }
 

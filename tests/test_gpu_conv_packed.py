@@ -109,3 +109,26 @@ def run(packed, mirror, W, b, x, aux, want, case):
         if w2 is not None:
             got2 = from_channels_last(host_bf16(out2), nb, channels, shape)
             np.testing.assert_array_equal(got2, w2, err_msg="epilogue %d out2" % epi)
+
+
+def test_bias_at_any_float():
+    """A bias that starts at any float of an array."""
+    announce("conv with a bias at an odd offset")
+    rng = _rng(11)
+    for cin, cout, nb, (lz, ly, lx) in ((16, 32, 1, (2, 2, 4)), (16, 64, 2, (1, 2, 3))):
+        shape = (1 << lz, 1 << ly, 1 << lx)
+        x = rng.integers(-4, 5, size=(nb, cin) + shape) / 4.0
+        W = rng.integers(-4, 5, size=(cout, 27, cin)) / 8.0
+        b = rng.integers(-8, 9, size=cout) / 16.0
+        acc = N.conv3(x, W, np.zeros(cout))
+        want = N.round_bf16(N.act(acc + b[None, :, None, None, None]))
+        from paper_2605_28800_amd import proposal as PR
+        for offset in (1, 2, 3):
+            store = torch.zeros(cout + 4, dtype=torch.float32, device="cuda")
+            bias = store[offset:offset + cout]
+            bias.copy_(torch.from_numpy(b.astype(np.float32)))
+            out = torch.empty((nb << (lz + ly + lx), cout), dtype=torch.int16, device="cuda")
+            PR.nn_conv3(0, dev_bf16(channels_last(x, cin)), weights_dev(W, cin, cout), bias, nb, lx,
+                        ly, lz, cin, cout, out=out)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(from_channels_last(host_bf16(out), nb, cout, shape), want)
