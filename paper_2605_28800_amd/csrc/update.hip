@@ -1098,13 +1098,23 @@ __global__ void k_rk_control(RkState *r, int nb, const double *__restrict__ part
     }
 }
 
-__global__ void k_rk_copy(const RkState *r, const uint2 *__restrict__ src, uint2 *__restrict__ dst,
-                          size_t n8, const unsigned *__restrict__ tail_src, unsigned *tail_dst)
+// (V: uint2, or single words where an odd number of floats lies before a buffer)
+template <typename V>
+__global__ void k_rk_copy(const RkState *r, const V *__restrict__ src, V *__restrict__ dst, size_t n)
 {
     if (r->keep) return;
-    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (size_t i = i0; i < n8; i += (size_t)gridDim.x * blockDim.x) dst[i] = src[i];
-    if (i0 == 0 && tail_dst) *tail_dst = *tail_src;       // an odd number of floats
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (size_t)gridDim.x * blockDim.x)
+        dst[i] = src[i];
+}
+
+template <typename V>
+static hipError_t rk_copy(const RkState *r, const void *src, void *dst, size_t bytes, hipStream_t s)
+{
+    const size_t n = bytes / sizeof(V), blocks = (n + 255) / 256;
+    hipLaunchKernelGGL(k_rk_copy<V>, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0,
+                       s, r, (const V *)src, (V *)dst, n);
+    return hipGetLastError();
 }
 
 hipError_t launch_rk_begin(RkState *r, int nb, double h, double atol, double rtol,
@@ -1123,14 +1133,8 @@ hipError_t launch_rk_control(RkState *r, int nb, const double *partials, int n, 
 hipError_t launch_rk_copy(const RkState *r, const void *src, void *dst, size_t bytes,
                           hipStream_t s)
 {
-    const size_t n8 = bytes / 8;
-    const size_t blocks = (n8 + 255) / 256;
-    const bool tail = (bytes & 4) != 0;
-    hipLaunchKernelGGL(k_rk_copy, dim3((unsigned)(blocks < 1 ? 1 : (blocks < 2048 ? blocks : 2048))),
-                       dim3(256), 0, s, r, (const uint2 *)src, (uint2 *)dst, n8,
-                       tail ? (const unsigned *)src + 2 * n8 : nullptr,
-                       tail ? (unsigned *)dst + 2 * n8 : nullptr);
-    return hipGetLastError();
+    const uintptr_t any = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) | bytes;
+    return any % 8 ? rk_copy<unsigned>(r, src, dst, bytes, s) : rk_copy<uint2>(r, src, dst, bytes, s);
 }
 
 // Fixed device scratch of the allocation-free energy entry point (energy

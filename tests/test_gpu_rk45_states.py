@@ -88,3 +88,26 @@ def test_first_decision_follows_the_error(n, prec, path):
     off = 5e-3 * 2 * rate * 0.18 * (8 * eps + field) / (1e-3 * err)
     assert abs(h / h1 - 1) <= off / 5 + 1e-12
     assert np.abs(got - want).max() <= (1e-5 if prec == "f32" else 1e-12) * np.abs(want).max()
+
+
+@pytest.mark.parametrize("n", [(9, 7, 5), (8, 7, 5), (1, 1, 1)])
+@pytest.mark.parametrize("nb", [0, 3])
+def test_odd_numbers_of_floats(n, nb):
+    """The second state buffer starts behind 3 * cells floats: on a single word
+    where that is odd.  Accepted states are copied whole: calls of one step (a
+    fresh look at P each) and one call of all give the same bits."""
+    announce("RK45 FP32 of %s, batch %d" % (n, nb))
+    cfg = _cfg(n)
+    P = np.stack([I.initial_P(cfg, s, np.float32) for s in range(max(nb, 1))])
+    got = []
+    for parts in ((9,), (1,) * 9):
+        ctx = _batch_context(cfg, "f32", nb, [300.0] * nb) if nb else gpu_context(cfg, "f32")
+        try:
+            ctx.set_P(P if nb else P[0])
+            for k in parts:
+                ctx.step(k)
+            got.append(ctx.get_P(PREC["f32"]))
+        finally:
+            ctx.close()
+    assert np.array_equal(got[0], got[1]) and np.isfinite(got[0]).all()
+    assert (got[0].reshape(P.shape) != P).any(axis=(1, 2, 3, 4)).all()
